@@ -78,6 +78,9 @@ typedef uint64_t e2e_ticket;
                                 tail, Numerical Recipes Sec. 6.2) and FP32 sums */
 #define E2E_PREC_BF16_HILO 2 /* separable only: bf16 hi/lo MFMA, FP32 sums     */
 #define E2E_PREC_F16_HILO 3  /* separable only: fp16 hi/lo MFMA, FP32 sums     */
+/* (separable FP32 frames whose traces hold enough samples per pixel are
+ * rendered from column nodes: FP64 weights rounded once to FP32, FP32 products
+ * of 16 nodes added to FP64 sums, at every precision) */
 
 /* request flags */
 #define E2E_FLAG_ASYNC 1u    /* device output: return once enqueued on stream  */

@@ -155,6 +155,7 @@ extern "C" e2e_status e2e_format_load(e2e_ctx *ctx, const e2e_trace_desc *tr, in
         return fail(E2E_EINVAL, "e2e_format_load: detector %dx%d", nx, ny);
     std::vector<TraceDev> h(n);
     int dxm = 0, dym = 0, nslots = 0;
+    double slope = 0, bend = 0, spans = 0, samples = 0;
     const int NG = 4097;
     for (int i = 0; i < n; ++i) {
         const e2e_trace_desc &d = tr[i];
@@ -218,6 +219,10 @@ extern "C" e2e_status e2e_format_load(e2e_ctx *ctx, const e2e_trace_desc *tr, in
         for (int g = 0; g < NG; ++g)
             y3 = std::max(y3, fabs(dpoly(T.cy, T.degy, -1.001 + h_t * g, 3)));
         T.y2max = maxy2 + y3 * h_t + 1e-9;
+        spans += poly(T.cx, T.degx, 1.0) - poly(T.cx, T.degx, -1.0);
+        samples += (double)T.n;
+        slope = std::max(slope, std::max(maxslope, slope_hi));
+        bend = std::max(bend, std::max(maxx2, T.y2max) / (xlow * xlow));
         dxm = std::max(dxm, T.degx);
         dym = std::max(dym, T.degy);
         nslots = std::max(nslots, T.slot + 1);
@@ -234,6 +239,9 @@ extern "C" e2e_status e2e_format_load(e2e_ctx *ctx, const e2e_trace_desc *tr, in
     F->nslots = nslots;
     F->degx = dxm;
     F->degy = dym;
+    F->slope = slope;
+    F->bend = bend;
+    F->density = samples / spans;
     F->host = h;
     F->bytes = bytes;
     hipError_t e = hipMalloc(&F->dev, bytes);
@@ -362,6 +370,18 @@ extern "C" e2e_status e2e_psf_load(e2e_ctx *ctx, const e2e_psf_desc *d, e2e_psf_
         sxy.assign(d->sigma_xy, d->sigma_xy + nn);
         for (float v : sxy)
             if (!(std::isfinite(v) && v > 0)) return bad(E2E_EPSF, "sigma_xy must be > 0");
+        P->smin[0] = P->smin[1] = 1e30;
+        for (int l = 0; l < d->grid_ny; ++l)
+            for (int m = 0; m < d->grid_nx; ++m)
+                for (int c = 0; c < 2; ++c) {
+                    auto at = [&](int ll, int mm) {
+                        return (double)sxy[((size_t)ll * d->grid_nx + mm) * 2 + c];
+                    };
+                    const double v = at(l, m);
+                    P->smin[c] = std::min(P->smin[c], v);
+                    if (m > 0) P->sstep[0] = std::max(P->sstep[0], fabs(v - at(l, m - 1)));
+                    if (l > 0) P->sstep[1] = std::max(P->sstep[1], fabs(v - at(l - 1, m)));
+                }
     } else if (d->kind == E2E_PSF_SFI) {
         if (d->half_width < 1 || d->half_width > kSfiMaxH)
             return bad(E2E_EPSF, "half_width outside 1..7");
@@ -523,7 +543,7 @@ Scratch *e2e::scratch_for(e2e_ctx *ctx, hipStream_t s)
     if (it != ctx->scratch.end()) return it->second;
     auto *sc = new Scratch();
     if (hipMalloc(&sc->err, sizeof(int)) != hipSuccess ||
-        hipMalloc(&sc->counter, sizeof(int)) != hipSuccess ||
+        hipMalloc(&sc->counter, kCounters * sizeof(int)) != hipSuccess ||
         hipHostMalloc((void **)&sc->err_host, sizeof(int)) != hipSuccess ||
         launch_fill_i32(sc->err, 1, 0, s) != hipSuccess) {
         free_scratch(sc);
@@ -570,9 +590,53 @@ e2e_status e2e::validate_req(e2e_ctx *ctx, const e2e_render_req *r, FormatRes **
     return E2E_OK;
 }
 
-static void tile_geom(const PsfRes *P, int precision, int *tw, int *th)
+// Nodes a pixel column of the separable path's FP32 frames (k_sep_fit.hip),
+// 0 for the per-sample kernels.  kappa bounds the inverse width of a
+// footprint along a trace (both axes, and the drift of sigma across a
+// column); the interpolation error 2.2 (kappa / 4)^M / sqrt(M!) of the peak
+// is kept below 4e-9, a tenth of the FP32 rounding of the frame: 10 nodes up
+// to kappa = 1.13 (sigma >= 0.9 px), 12 up to 1.72 (sigma >= 0.58 px, also
+// where the kernel's eight-term pixel integrals end).  The measured error of
+// the frames is no larger than the per-sample kernels' (5e-8 of the norm).
+// FP64 frames keep the per-sample sums: the nodes change a pixel by more
+// than their last places.  Strongly bent formats (few pixels per radian of
+// curvature) keep them too: the nodes' positions take two Newton steps.  So
+// do sparse samplings, where a column holds few more samples than nodes: a
+// 4096^2 frame (80 traces, H = 8) takes 0.45 ms at 6 and 0.66 ms at 10 to 60
+// samples a pixel here, against 0.55 (FP64), 0.40 (FP32), 0.36 ms (hi/lo) at
+// 6, 0.92 / 0.65 / 0.59 at 12, 1.00 / 0.73 / 0.67 at 14 and 3.6 / 2.5 / 2.3 at
+// 60 per sample.  Frames of few tiles wait for one tile's chain of traces
+// (700^2: 0.12 ms here at 10 to 60 samples a pixel; 0.11 / 0.09 / 0.14 at 20,
+// 0.15 / 0.12 / 0.19 at 30 and 0.25 / 0.19 / 0.34 at 60 per sample; 1500^2,
+// above the line of 768 tiles: 0.15 ms here, 0.19 / 0.16 / 0.12 at 10).
+static int sep_fit_nodes(const FormatRes *F, const PsfRes *P, int precision, int out_dtype)
 {
-    if (P->kind == E2E_PSF_TABLE) {
+    if (P->kind != E2E_PSF_SEPARABLE || out_dtype != E2E_F32) return 0;
+    if (F->ntr > kSepFitMaxTraces || F->bend > 1e-2) return 0;
+    const int tiles = ((F->nx + kMfmaTW - 1) / kMfmaTW) * ((F->ny + kMfmaTH - 1) / kMfmaTH);
+    const bool few = tiles < kSepFitTiles;
+    const double dense = precision == E2E_PREC_F64   ? (few ? 22.0 : 6.0)
+                         : precision == E2E_PREC_F32 ? (few ? 34.0 : 13.0)
+                                                     : (few ? 15.0 : 14.0);
+    if (F->density < dense) return 0;
+    const double gsx = P->gx > 1 && F->nx > 1 ? (double)(P->gx - 1) / (F->nx - 1) : 0.0;
+    const double gsy = P->gy > 1 && F->ny > 1 ? (double)(P->gy - 1) / (F->ny - 1) : 0.0;
+    const double drift = 2.0 * (P->sstep[0] * gsx + P->sstep[1] * gsy * F->slope) /
+                         std::min(P->smin[0], P->smin[1]);
+    const double kappa = std::hypot(1.0 / P->smin[0], F->slope / P->smin[1]) + drift;
+    // the pixel integrals' own series, on either axis
+    if (std::min(P->smin[0], P->smin[1]) < 0.58) return 0;
+    for (int M = 10; M <= 12; M += 2)
+        if (2.2 * std::pow(kappa / 4.0, M) <= 4e-9 * std::sqrt(std::tgamma(M + 1.0))) return M;
+    return 0;
+}
+
+static void tile_geom(const PsfRes *P, int precision, int nodes, int *tw, int *th)
+{
+    if (nodes > 0) {
+        *tw = kMfmaTW;
+        *th = kMfmaTH;
+    } else if (P->kind == E2E_PSF_TABLE) {
         *tw = table_tw(P->kw);
         *th = kTableTH;
     } else if (P->kind == E2E_PSF_SEPARABLE &&
@@ -647,13 +711,14 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
     cfg.resident = tr[0].resident;
     size_t seg_total = 0;
     std::vector<size_t> seg_off(n);
-    std::vector<int> tiles(n);
+    std::vector<int> tiles(n), nodes(n);
     int nslots_total = 0;
     std::vector<int> spec_off(n);
     size_t temp_bytes = 0;
     for (int i = 0; i < n; ++i) {
         int tw, th;
-        tile_geom(ps[i], prec, &tw, &th);
+        nodes[i] = sep_fit_nodes(fs[i], ps[i], prec, reqs[i].out_dtype);
+        tile_geom(ps[i], prec, nodes[i], &tw, &th);
         int ntx = (fs[i]->nx + tw - 1) / tw, nty = (fs[i]->ny + th - 1) / th;
         tiles[i] = kind == E2E_PSF_TABLE ? table_units(ntx, nty, tr[i].chunk) : ntx * nty;
         seg_off[i] = seg_total;
@@ -740,7 +805,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         FormatRes *fm = fs[i];
         PsfRes *P = ps[i];
         int tw, th;
-        tile_geom(P, prec, &tw, &th);
+        tile_geom(P, prec, nodes[i], &tw, &th);
         F.tr = fm->dev;
         F.spec = sc->specptrs + spec_off[i];
         if (r.out_on_device) {
@@ -787,6 +852,14 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
     cfg.plain_tiles = tiles[0];
     // work list: frames by decreasing size, tiles in order
     sc->h_work.clear();
+    // the frames of one launch share a kernel: work items [w0, w1) of each
+    // node count present (separable frames; other kinds have one group)
+    struct Group {
+        int nodes;
+        size_t w0, w1;
+    };
+    std::vector<Group> groups;
+    if (!batch) groups.push_back({nodes[0], 0, 0});
     if (batch) {
         std::vector<int> order(n);
         for (int i = 0; i < n; ++i) order[i] = i;
@@ -796,12 +869,20 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         // frames of equal size go unit by unit, so the same unit of each (the
         // same spectrum ranges, read again under another Doppler shift) runs
         // at about the same time and its reads hit the caches
-        for (size_t g = 0; g < order.size();) {
-            size_t h = g;
-            while (h < order.size() && tiles[order[h]] == tiles[order[g]]) ++h;
-            for (int t = 0; t < tiles[order[g]]; ++t)
-                for (size_t q = g; q < h; ++q) sc->h_work.push_back(make_int2(order[q], t));
-            g = h;
+        for (int nn : {0, 10, 12}) {
+            std::vector<int> own;
+            for (int i : order)
+                if (nodes[i] == nn) own.push_back(i);
+            if (own.empty()) continue;
+            const size_t w0 = sc->h_work.size();
+            for (size_t g = 0; g < own.size();) {
+                size_t h = g;
+                while (h < own.size() && tiles[own[h]] == tiles[own[g]]) ++h;
+                for (int t = 0; t < tiles[own[g]]; ++t)
+                    for (size_t q = g; q < h; ++q) sc->h_work.push_back(make_int2(own[q], t));
+                g = h;
+            }
+            groups.push_back({nn, w0, sc->h_work.size()});
         }
     }
     if (noalloc) {
@@ -850,34 +931,41 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         return hip_fail(e, "error word");
     bool any_noise = false;
     for (int i = 0; i < n; ++i) any_noise |= reqs[i].poisson != 0;
-    const int2 *work = batch ? sc->work : nullptr;
-    const int nwork = batch ? (int)work_n : 0;
     // the launch sequence: clear error word and queue counter, plan, render, noise
     auto enqueue = [&]() -> hipError_t {
         hipError_t q;
         // the error word is sticky (cleared after a synchronous read), so an
         // asynchronous launch's device error reaches the next synchronous call
-        if ((q = launch_fill_i32(sc->counter, 1, 0, s)) != hipSuccess) return q;
+        if ((q = launch_fill_i32(sc->counter, (int)groups.size(), 0, s)) != hipSuccess) return q;
         prof_begin(ctx, s, "plan");
         q = launch_plan(sc->frames_dev, sc->h_frames.data(), n, sc->err, s);
         prof_end(ctx, s);
         if (q != hipSuccess) return q;
-        if (kind == E2E_PSF_TABLE) {
-            prof_begin(ctx, s, "render_table");
-            q = launch_table(sc->frames_dev, cfg, work, nwork, sc->counter, sc->err, s);
-        } else if (kind == E2E_PSF_SEPARABLE &&
-                   (prec == E2E_PREC_BF16_HILO || prec == E2E_PREC_F16_HILO)) {
-            prof_begin(ctx, s, "render_sep_mfma");
-            q = launch_sep_mfma(sc->frames_dev, cfg, work, nwork, sc->counter, sc->err, s);
-        } else if (kind == E2E_PSF_SFI) {
-            prof_begin(ctx, s, "render_sfi");
-            q = launch_sfi(sc->frames_dev, cfg, work, nwork, sc->counter, sc->err, s);
-        } else {
-            prof_begin(ctx, s, "render_sep");
-            q = launch_sep(sc->frames_dev, cfg, work, nwork, sc->counter, sc->err, s);
+        const bool mfma = prec == E2E_PREC_BF16_HILO || prec == E2E_PREC_F16_HILO;
+        const char *name = kind == E2E_PSF_TABLE ? "render_table"
+                           : kind == E2E_PSF_SFI ? "render_sfi"
+                           : kind == E2E_PSF_SEPARABLE && mfma ? "render_sep_mfma"
+                                                               : "render_sep";
+        for (size_t g = 0; g < groups.size(); ++g) {
+            const int2 *work = batch ? sc->work + groups[g].w0 : nullptr;
+            const int nwork = (int)(groups[g].w1 - groups[g].w0);
+            int *counter = sc->counter + g;
+            KernelCfg kc = cfg;
+            kc.nodes = groups[g].nodes;
+            prof_begin(ctx, s, name);
+            if (kind == E2E_PSF_TABLE)
+                q = launch_table(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
+            else if (kc.nodes > 0)
+                q = launch_sep_fit(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
+            else if (kind == E2E_PSF_SEPARABLE && mfma)
+                q = launch_sep_mfma(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
+            else if (kind == E2E_PSF_SFI)
+                q = launch_sfi(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
+            else
+                q = launch_sep(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
+            prof_end(ctx, s);
+            if (q != hipSuccess) return q;
         }
-        prof_end(ctx, s);
-        if (q != hipSuccess) return q;
         if (any_noise) {
             prof_begin(ctx, s, "noise");
             q = launch_noise_frames(sc->frames_dev, sc->h_frames.data(), n, s);
@@ -897,9 +985,12 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
             maxw = std::max(maxw, sc->h_frames[i].ntx * sc->h_frames[i].ntr);
             maxpix = std::max(maxpix, (int64_t)sc->h_frames[i].nx * sc->h_frames[i].ny);
         }
-        char key[256];
-        snprintf(key, sizeof key, "%d/%d/%d/%d/%d/%d/%d/%d/%zu/%d/%lld/%d/%p/%p", kind, cfg.kw,
-                 cfg.resident, cfg.degx, cfg.degy, cfg.spec_f64, prec, n, work_n, maxw,
+        std::string parts;  // the render launches: node count and items of each
+        for (auto &g : groups)
+            parts += std::to_string(g.nodes) + ":" + std::to_string(g.w1 - g.w0) + ",";
+        char key[320];
+        snprintf(key, sizeof key, "%d/%d/%d/%d/%d/%d/%d/%d/%s/%d/%lld/%d/%p/%p", kind, cfg.kw,
+                 cfg.resident, cfg.degx, cfg.degy, cfg.spec_f64, prec, n, parts.c_str(), maxw,
                  any_noise ? (long long)maxpix : 0ll, (int)any_noise, (void *)sc->frames_dev,
                  (void *)sc->work);
         auto it = sc->graphs.find(key);

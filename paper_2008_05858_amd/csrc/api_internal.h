@@ -19,6 +19,9 @@ namespace e2e {
 
 struct FormatRes {
     int nx = 0, ny = 0, ntr = 0, nslots = 0, degx = 0, degy = 0;
+    double slope = 0;      // bound on |dy/dx| over the traces
+    double density = 0;    // samples per pixel column, mean over the traces
+    double bend = 0;       // bound on |x''|, |y''| per pixel (over min(x')^2)
     std::vector<TraceDev> host;
     TraceDev *dev = nullptr;
     size_t bytes = 0;
@@ -31,6 +34,8 @@ struct PsfRes {
     int H = 0, gx = 1, gy = 1, kw = 0, kh = 0, os = 0;
     uint16_t *tfrag = nullptr;  // table taps as fp16 hi/lo product fragments
     float *sxy = nullptr;   // separable sigma grid
+    double smin[2] = {0, 0};  // separable: smallest sigma_x, sigma_y of the grid
+    double sstep[2] = {0, 0}; // separable: largest sigma step between nodes along x, y
     float *sfq = nullptr;   // SFI: quadrature nodes [R][3]
     int sfi_R = 0, sfi_S = 0, sfi_shape = 0;
     double rho = 0;

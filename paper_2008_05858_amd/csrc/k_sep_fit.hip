@@ -1,0 +1,743 @@
+// Separable-PSF render path for FP32 frames (Sec. 2.1's axis-aligned
+// Gaussian aberration model with field-dependent (sigma_x, sigma_y)): the
+// samples of one trace in one pixel column are first gathered onto a few
+// nodes, then the nodes are rendered.
+//
+// Within one pixel column of a trace (the samples with floor(x + 1/2) = i)
+// and one row anchor, a sample's footprint is a smooth function of its
+// offset s = x - i in [-1/2, 1/2): both windows stand still, and y, sigma_x
+// and sigma_y vary smoothly along the trace.  So the footprint is taken as
+// its Chebyshev interpolant on the M nodes s_m,
+//     w(s) = sum_m L_m(s) w(s_m),
+// and the column's samples add up to M node weights
+//     sum_k phi_k w(s_k) = sum_m Phi_m w(s_m),
+//     Phi_m = sum_k phi_k L_m(s_k) = 1/M (mu_0 + 2 sum_{p>=1} mu_p T_p(2 s_m)),
+//     mu_p = sum_k phi_k T_p(2 s_k),
+// FP64 sums over the samples by the recurrence of phi T_p.  For a Gaussian of
+// inverse width kappa along the trace the interpolation error is below
+// 2.2 (kappa / 4)^M / sqrt(M!) of the footprint's peak (Cramer's bound on the
+// Hermite functions): the host picks M = 10 or 12 so that this stays below
+// 4e-9 (sep_fit_nodes), a tenth of the FP32 rounding of the frame.  Columns
+// where the footprint is not smooth (a line of the sigma grid crosses them,
+// the trace begins or ends in them) or that hold no more than M + 1 samples
+// render their samples one by one.
+//
+// What bounds it: the C2-shaped frame (9216^2, 340 traces, 108 samples a
+// column) used to evaluate 36 normal CDFs for each of 3.4e8 samples in every
+// tile it reaches, VALU issue in all of the per-sample kernels.  Here a sample
+// costs ~30 FP64 instructions and a tenth as many nodes the pixel integrals:
+// 56.8 ms (FP64 VALU) and 35.0 ms (fp16 hi/lo MFMA) -> 5.4 ms at either
+// precision, still VALU issue (about 2e9 instructions, two thirds of the
+// issue slots) on the node's pixel integrals and the column sums.
+//
+// A workgroup owns a 64 x 32 tile, three of them fit a CU (LDS).  Per trace:
+// the first sample of each column (exact test on the FP64 format), the column
+// list, then for batches of columns: four lanes a column add up the moments
+// and write the nodes' photons to LDS; then per chunk of 120 nodes one thread
+// per (node, axis) stores the node's pixel integrals on the tile's 64 columns
+// (times photons) or 32 rows as FP32, and finds the next chunk's position and
+// sigma; wave w multiplies column block w, F += Gy diag(Phi) Gx^T, by
+// v_mfma_f32_16x16x4_f32 over 16 nodes at a time, each FP32 partial then added
+// to FP64 sums.  One form serves all precisions: FP64 products
+// (v_mfma_f64_16x16x4_f64) took 6.8 ms, FP32 sums throughout 5.5 ms, fp16
+// hi/lo halves 6.4 ms (splitting the weights costs more than the matrix cores
+// save), and this is also the closest to the exact frame of the last three.
+// Pixel integrals are taken in FP64: P(z) = 2a phi(z) sum_i A_i (z a)^(2i) /
+// (2i)!, a = h / 2 = 1 / (2 sigma), from exp(-z u) expanded under the integral
+// over the pixel (A_i = int_0^1 v^(2i) exp(-a^2 v^2 / 2) dv by its downward
+// recurrence); the Gaussian runs along the window by two multiplications a
+// pixel.  Eight terms leave an absolute error below 4e-10 for sigma >= 0.58.
+// The order of every sum is fixed: the result is deterministic.
+#include "psf_gauss.h"
+
+namespace e2e {
+
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int TX = kMfmaTW;            // 64 columns = 4 blocks of 16, one per wave
+constexpr int TY = kMfmaTH;            // 32 rows = 2 blocks of 16
+constexpr int CH = 120;                // nodes per chunk (12 columns of 10, 10 of 12)
+constexpr int LS = CH + 4;             // floats of a line in LDS, see lds_at
+constexpr int NCOL = TX + 2 * kMaxH;   // pixel columns whose samples reach the tile
+constexpr int NENT = 2 * NCOL;         // list entries: at most two row anchors a column
+
+// cos((2m + 1) pi / (2M)): the nodes are s_m = half of these
+__device__ constexpr double kNode10[10] = {
+    0.98768834059513777, 0.8910065241883679, 0.70710678118654757, 0.4539904997395468,
+    0.15643446504023092, -0.15643446504023092, -0.4539904997395468, -0.70710678118654757,
+    -0.8910065241883679, -0.98768834059513777};
+__device__ constexpr double kNode12[12] = {
+    0.99144486137381038, 0.92387953251128674, 0.79335334029123517, 0.60876142900872066,
+    0.38268343236508984, 0.13052619222005171, -0.13052619222005171, -0.38268343236508984,
+    -0.60876142900872066, -0.79335334029123517, -0.92387953251128674, -0.99144486137381038};
+// list entry: pixel column, row anchor (relative to the tile, + kMaxH), flags
+constexpr unsigned kEntRaw = 1u << 14;   // samples one by one
+constexpr unsigned kEntTest = 1u << 13;  // only the samples with this row anchor
+__device__ __forceinline__ unsigned ent_pack(int col, int arow)
+{
+    return (unsigned)col | ((unsigned)(arow + kMaxH) << 7);
+}
+
+// Float index of (pixel line p, node s): the operands of one chunk in LDS are
+// [line][node] FP32 weights, four floats of zeros after each line.  Lines are
+// 124 floats apart, so the 16 lines that a fragment read touches start on
+// different banks and a thread's writes go down the lines at a fixed step.
+__device__ __forceinline__ int lds_at(int p, int s) { return p * LS + s; }
+
+// 1 / v for v > 0: the hardware reciprocal and two Newton steps
+__device__ __forceinline__ double recip(double v)
+{
+    double r = __builtin_amdgcn_rcp(v);
+    r = fma(r, fma(-v, r, 1.0), r);
+    return fma(r, fma(-v, r, 1.0), r);
+}
+
+// exp(x) for x in [-0.4, 0]: Taylor to x^9 (truncation below 3e-11)
+__device__ __forceinline__ double exp_small(double x)
+{
+    double p = fma(x, 1.0 / 362880.0, 1.0 / 40320.0);
+    p = fma(p, x, 1.0 / 5040.0);
+    p = fma(p, x, 1.0 / 720.0);
+    p = fma(p, x, 1.0 / 120.0);
+    p = fma(p, x, 1.0 / 24.0);
+    p = fma(p, x, 1.0 / 6.0);
+    p = fma(p, x, 0.5);
+    p = fma(p, x, 1.0);
+    return fma(p, x, 1.0);
+}
+
+// exp(x) for |x| < 700: 2^n times exp of the remainder, |r| <= ln2 / 2
+// (Taylor to r^9, relative error below 1e-11)
+__device__ __forceinline__ double exp_mid(double x)
+{
+    const double n = rint(x * 1.4426950408889634);
+    const double r = fma(n, -0.6931471805599453, x);
+    return ldexp(exp_small(r), (int)n);
+}
+
+// Pixel integrals of one Gaussian (sigma sg, centre d from the anchor pixel)
+// on NL pixel lines: window pixel m (0 .. 2H) lies on line off + m and gets
+// its integral times scale / window sum.  Writes the in-tile entries and
+// returns their line range (empty: *plo > *phi).
+template <int NL>
+__device__ __forceinline__ void stage_axis(double d, double sg, int H, double scale, int off,
+                                           int s, float *b, int *plo, int *phi)
+{
+    const int m0 = max(0, -off), m1 = min(2 * H, NL - 1 - off);
+    *plo = off + m0;
+    *phi = off + m1;
+    if (m0 > m1) return;
+    const double h = recip(sg), a = 0.5 * h, a2 = a * a;
+    const double e0 = exp_small(-0.5 * a2);
+    // A_8 by its ascending series, then downward (all terms positive)
+    double A = e0 * fma(a2, fma(a2, fma(a2, 1.0 / 156009.0, 1.0 / 6783.0), 1.0 / 323.0), 1.0 / 17.0);
+    A = fma(a2, A, e0) * (1.0 / 15.0);
+    const double c7 = A * (1.0 / 87178291200.0);
+    A = fma(a2, A, e0) * (1.0 / 13.0);
+    const double c6 = A * (1.0 / 479001600.0);
+    A = fma(a2, A, e0) * (1.0 / 11.0);
+    const double c5 = A * (1.0 / 3628800.0);
+    A = fma(a2, A, e0) * (1.0 / 9.0);
+    const double c4 = A * (1.0 / 40320.0);
+    A = fma(a2, A, e0) * (1.0 / 7.0);
+    const double c3 = A * (1.0 / 720.0);
+    A = fma(a2, A, e0) * (1.0 / 5.0);
+    const double c2 = A * (1.0 / 24.0);
+    A = fma(a2, A, e0) * (1.0 / 3.0);
+    const double c1 = A * 0.5;
+    const double c0 = fma(a2, A, e0);
+    // the window's outer edges lie in the far tail: the fitted FP32 tail's
+    // relative error there is below 2e-7 of Phi(-H / sigma)
+    const float ta = phi_tail_f32((float)(((double)(-H) - 0.5 - d) * h));
+    const float tb = phi_tail_f32((float)(((double)H + 0.5 - d) * h));
+    const double f = scale * 0.3989422804014327 * h * recip((1.0 - (double)ta) - (double)tb);
+    double z = ((double)(m0 - H) - d) * h;
+    double E = f * exp_mid(-0.5 * z * z), r = exp_mid(-h * fma(0.5, h, z));
+    double q = e0 * e0;
+    q *= q;
+    q *= q;
+    double w = z * a;
+    const double dw = h * a;
+    // two pixels a turn: two independent chains
+    const double q2 = q * q, rq = r * r * q, dw2 = dw + dw;
+    double E1 = E * r, w1 = w + dw;
+    double g0 = rq, g1 = rq * q2;  // E_{m+2} / E_m, E_{m+3} / E_{m+1}
+    float *at = b + lds_at(off + m0, s);
+    const double q4 = q2 * q2;
+    for (int m = m0; m <= m1; m += 2) {
+        const double v0 = w * w, v1 = w1 * w1;
+        double p0 = fma(c7, v0, c6), p1 = fma(c7, v1, c6);
+        p0 = fma(p0, v0, c5);
+        p1 = fma(p1, v1, c5);
+        p0 = fma(p0, v0, c4);
+        p1 = fma(p1, v1, c4);
+        p0 = fma(p0, v0, c3);
+        p1 = fma(p1, v1, c3);
+        p0 = fma(p0, v0, c2);
+        p1 = fma(p1, v1, c2);
+        p0 = fma(p0, v0, c1);
+        p1 = fma(p1, v1, c1);
+        p0 = fma(p0, v0, c0);
+        p1 = fma(p1, v1, c0);
+        at[0] = (float)(E * p0);
+        if (m < m1) at[LS] = (float)(E1 * p1);
+        at += 2 * LS;
+        E *= g0;
+        E1 *= g1;
+        g0 *= q4;
+        g1 *= q4;
+        w += dw2;
+        w1 += dw2;
+    }
+}
+
+// zero lines [zlo, zhi] of sample slot s except [nlo, nhi]
+__device__ __forceinline__ void clear_lines(int zlo, int zhi, int nlo, int nhi, int s,
+                                            float *b)
+{
+    const bool none = nlo > nhi;
+    const int e1 = none ? zhi : min(zhi, nlo - 1);
+    for (int p = zlo; p <= e1; ++p) b[lds_at(p, s)] = 0.0f;
+    if (!none)
+        for (int p = max(zlo, nhi + 1); p <= zhi; ++p) b[lds_at(p, s)] = 0.0f;
+}
+
+// 16-line blocks covered by lines [lo, hi]
+__device__ __forceinline__ unsigned block_bits(int lo, int hi)
+{
+    if (lo > hi) return 0u;
+    const int b0 = lo >> 4, b1 = hi >> 4;
+    return ((2u << b1) - 1u) & ~((1u << b0) - 1u);
+}
+
+// One axis' sigma of a sample, bilinear in the field over the node grid.
+__device__ __forceinline__ double sigma_axis(const float *sxy, int gx, int gy, double gsx,
+                                             double gsy, double x, double y, int c)
+{
+    double fx, fy;
+    const int cx = node_cell(x, gsx, gx, &fx), cy = node_cell(y, gsy, gy, &fy);
+    const int cx1 = min(cx + 1, gx - 1), cy1 = min(cy + 1, gy - 1);
+    const float s00 = sxy[(cy * gx + cx) * 2 + c], s01 = sxy[(cy * gx + cx1) * 2 + c];
+    const float s10 = sxy[(cy1 * gx + cx) * 2 + c], s11 = sxy[(cy1 * gx + cx1) * 2 + c];
+    const double lo = fma(fx, (double)s01 - (double)s00, (double)s00);
+    const double hi = fma(fx, (double)s11 - (double)s10, (double)s10);
+    return fma(fy, hi - lo, lo);
+}
+
+// v added over the four lanes of a quad (the same bits in each)
+__device__ __forceinline__ double quad_sum(double v)
+{
+    long long b = __double_as_longlong(v);
+    int lo = (int)(b & 0xffffffffll), hi = (int)(b >> 32);
+    int l1 = __builtin_amdgcn_update_dpp(0, lo, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
+    int h1 = __builtin_amdgcn_update_dpp(0, hi, 0xB1, 0xF, 0xF, true);
+    v += __longlong_as_double(((long long)h1 << 32) | (unsigned)l1);
+    b = __double_as_longlong(v);
+    lo = (int)(b & 0xffffffffll);
+    hi = (int)(b >> 32);
+    l1 = __builtin_amdgcn_update_dpp(0, lo, 0x4E, 0xF, 0xF, true);      // quad_perm [2,3,0,1]
+    h1 = __builtin_amdgcn_update_dpp(0, hi, 0x4E, 0xF, 0xF, true);
+    return v + __longlong_as_double(((long long)h1 << 32) | (unsigned)l1);
+}
+
+template <typename ST>
+struct Vec4;
+template <>
+struct Vec4<float> {
+    __device__ static void load(const float *p, int k, float v[4])
+    {
+        const f4u q = *reinterpret_cast<const __attribute__((address_space(1))) f4u *>(as_global(p + k));
+        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    }
+};
+template <>
+struct Vec4<double> {
+    __device__ static void load(const double *p, int k, double v[4])
+    {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = p[k + e];
+    }
+};
+
+template <int DX, int DY, typename ST, int M>
+__global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__restrict__ frames,
+                                                           const int2 *__restrict__ work,
+                                                           int n_work, int *__restrict__ counter,
+                                                           int *__restrict__ err)
+{
+    constexpr int BE = M == 10 ? 60 : 50;   // list entries per batch (4 lanes each)
+    static_assert(TX == 64 && TY == 32 && CH == 120, "block geometry");
+    static_assert((TX + TY) * LS % 4 == 0, "zeroed by 16-byte words");
+    static_assert(NCOL <= 128 && TY + 2 * kMaxH < 64, "entry fields");
+    __shared__ __attribute__((aligned(16))) float buf[(TX + TY) * LS];
+    __shared__ float sphi[BE][M];           // node photons of the batch
+    __shared__ int kst[NCOL + 1];           // first sample of each column
+    __shared__ int noff[BE + 1];            // first node of each entry of the batch
+    __shared__ unsigned short ent[NENT];
+    __shared__ unsigned short tlist[kMaxTileTraces];
+    __shared__ unsigned smask[4][2];
+    __shared__ double snode[M];             // 2 s_m
+    __shared__ int sh_item, sh_nent, sh_raw;
+    float *const ybuf = buf + TX * LS;       // the rows' lines follow the columns'
+
+    const int tid = threadIdx.x;
+    if (tid < M) snode[tid] = M == 10 ? kNode10[tid % 10] : kNode12[tid];
+    const int lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lg = lane >> 4;
+    // staging role: node slot s of the chunk, axis (x: waves 0-1, y: 2-3)
+    const int s = tid & 127;
+    const bool xaxis = tid < 128;
+
+    for (int iter = 0;; ++iter) {
+        int fi, tile_id;
+        if (work == nullptr) {
+            if (iter > 0) break;
+            fi = 0;
+            tile_id = xcd_remap(blockIdx.x, gridDim.x);
+        } else {
+            if (tid == 0) sh_item = atomicAdd(counter, 1);
+            __syncthreads();
+            const int w = uniform_i(sh_item);
+            if (w >= n_work) break;
+            const int2 wk = work[w];
+            fi = uniform_i(wk.x);
+            tile_id = uniform_i(wk.y);
+        }
+        const FrameDev &F = frames[fi];
+        const int ntr = F.ntr, H = F.H;
+        const int tx = tile_id % F.ntx, ty = tile_id / F.ntx;
+        const int X0 = tx * TX, Y0 = ty * TY;
+        const int ncol = min(TX, F.nx - X0) + 2 * H;
+        const SegDev *segs = F.segs + (size_t)tx * ntr;
+        // ---- traces that reach the tile, ascending: 256 tested at a time
+        int count = 0;
+        for (int base = 0; base < ntr; base += 256) {
+            const int tr = base + tid;
+            bool ok = false;
+            if (tr < ntr) {
+                const SegDev sv = segs[tr];
+                ok = sv.k0 < sv.k1 && sv.ty0 <= ty && ty <= sv.ty1;
+            }
+            const unsigned long long m = __ballot(ok);
+            const int par = (base >> 8) & 1;  // two sets of counts: one barrier a turn
+            if (lane == 0) smask[wv][par] = (unsigned)__popcll(m);
+            __syncthreads();
+            int pos = count + __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int v = (int)smask[w][par];
+                pos += w < wv ? v : 0;
+                count += v;
+            }
+            if (ok) {
+                if (pos < kMaxTileTraces) tlist[pos] = (unsigned short)tr;
+                else atomicOr(err, kErrTileTraces);
+            }
+        }
+        count = uniform_i(min(count, kMaxTileTraces));
+        // the staging planes start at zero
+        {
+            const uint4 zz = {0u, 0u, 0u, 0u};
+            uint4 *b4 = reinterpret_cast<uint4 *>(buf);
+            for (int q = tid; q < (TX + TY) * LS / 4; q += 256) b4[q] = zz;
+        }
+        __syncthreads();
+        int zlo = 1, zhi = 0;  // lines this thread's node slot holds (none)
+        double acc[2][4];
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[rb][q] = 0.0;
+
+        for (int li = 0; li < count; ++li) {
+            const int tr = uniform_i((int)tlist[li]);
+            const TraceDev &T = F.tr[tr];
+            const SegDev sg = segs[tr];
+            double cxr[DX + 1], cyr[DY + 1];
+#pragma unroll
+            for (int j = 0; j <= DX; ++j) cxr[j] = T.cx[j];
+#pragma unroll
+            for (int j = 0; j <= DY; ++j) cyr[j] = T.cy[j];
+            const TraceFrameDev &TF = F.tf[tr];
+            const double t0 = TF.t0, dt = TF.dt;
+            const float scale = (float)TF.scale;
+            const ST *spec = (const ST *)TF.spec;
+            const int nsamp = T.n;
+
+            // ---- first sample of each pixel column X0 - H + c (the sample's
+            // own test floor(x + 1/2) >= column), inside the planner's range
+            if (tid <= ncol) {
+                const int k0 = sg.k0, k1 = sg.k1;
+                const double col = (double)(X0 - H + tid);
+                auto xp = [&](int k) { return horner<DX>(cxr, fma((double)k, dt, t0)) + 0.5; };
+                const int km = k0 + ((k1 - 1 - k0) >> 1);
+                const double ua = xp(k0), um = xp(km), ub = xp(k1 - 1);
+                int k;
+                if (ua >= col) k = k0;
+                else if (ub < col) k = k1;
+                else {
+                    // quadratic guess through three samples, then exact: the
+                    // bracket [lo, hi] is widened from the guess and bisected
+                    double d1 = (double)(k1 - 1 - k0) / (ub - ua), d2 = 0.0;
+                    if (km > k0 && km < k1 - 1) {
+                        d1 = (double)(km - k0) / (um - ua);
+                        d2 = ((double)(k1 - 1 - km) / (ub - um) - d1) / (ub - ua);
+                    }
+                    const double g = ceil(fma(col - ua, fma(col - um, d2, d1), (double)k0));
+                    k = min(max((int)fmin(fmax(g, (double)k0), (double)k1), k0 + 1), k1 - 1);
+                    int lo = k0 + 1, hi = k1 - 1;  // the answer lies in [k0 + 1, k1 - 1]
+                    if (xp(k) >= col) {
+                        hi = k;
+                        for (int step = 1; hi > lo; step *= 2) {
+                            const int c = max(lo, hi - step);
+                            if (xp(c) >= col) hi = c;
+                            else { lo = c + 1; break; }
+                        }
+                    } else {
+                        lo = k + 1;
+                        for (int step = 1; lo < hi; step *= 2) {
+                            const int c = min(hi, lo + step - 1);
+                            if (xp(c) < col) lo = c + 1;
+                            else { hi = c; break; }
+                        }
+                    }
+                    while (lo < hi) {
+                        const int mid = lo + ((hi - lo) >> 1);
+                        if (xp(mid) >= col) hi = mid; else lo = mid + 1;
+                    }
+                    k = lo;
+                }
+                kst[tid] = k;
+            }
+            __syncthreads();
+
+            // ---- the columns that reach the tile's rows, one entry for each
+            // row anchor (at most two, |dy/dx| <= 1/2), in column order
+            if (wv == 0) {
+                int n = 0;
+                bool any_raw = false;
+                for (int base = 0; base < ncol; base += 64) {
+                    const int c = base + lane;
+                    unsigned e0 = 0, e1 = 0;
+                    int ne = 0;
+                    if (c < ncol) {
+                        const int ks = kst[c], ke = kst[c + 1];
+                        if (ks < ke) {
+                            const double ta = fma((double)ks, dt, t0);
+                            const double tb = fma((double)(ke - 1), dt, t0);
+                            const double ya = horner<DY>(cyr, ta), yb = horner<DY>(cyr, tb);
+                            // |y - chord| <= y2max (tb - ta)^2 / 8
+                            const double mg = fma(T.y2max, (tb - ta) * (tb - ta), 1e-9);
+                            const double yl = fmin(ya, yb) - mg, yh = fmax(ya, yb) + mg;
+                            const int al = (int)floor(yl + 0.5), ah = (int)floor(yh + 0.5);
+                            if (ah + H >= Y0 && al - H < Y0 + TY) {
+                                const double xc = (double)(X0 - H + c);
+                                // a line of the sigma grid in the column (the
+                                // nodes reach up to a sample past its ends in y)
+                                const double ext = (yh - yl) / (double)max(ke - ks - 1, 1) + 1e-6;
+                                const bool kink =
+                                    ext_cell(xc - 0.500001, F.gsx, F.gx) !=
+                                        ext_cell(xc + 0.500001, F.gsx, F.gx) ||
+                                    ext_cell(yl - ext, F.gsy, F.gy) != ext_cell(yh + ext, F.gsy, F.gy);
+                                const bool raw = ke - ks < M + 2 || ks == 0 || ke == nsamp || kink ||
+                                                 ah > al + 1;
+                                if (raw) {
+                                    e0 = (unsigned)c | kEntRaw;
+                                    ne = 1;
+                                    any_raw = true;
+                                } else {
+                                    const bool two = al != ah;
+                                    const bool in0 = al + H >= Y0 && al - H < Y0 + TY;
+                                    const bool in1 = two && ah + H >= Y0 && ah - H < Y0 + TY;
+                                    const unsigned tst = two ? kEntTest : 0u;
+                                    const unsigned p0 = in0 ? ent_pack(c, al - Y0) | tst : 0u;
+                                    const unsigned p1 = in1 ? ent_pack(c, ah - Y0) | tst : 0u;
+                                    e0 = in0 ? p0 : p1;
+                                    e1 = p1;
+                                    ne = (in0 ? 1 : 0) + (in1 ? 1 : 0);
+                                }
+                            }
+                        }
+                    }
+                    const unsigned long long b1 = __ballot(ne >= 1), b2 = __ballot(ne == 2);
+                    const unsigned long long below = (1ull << lane) - 1ull;
+                    const int pos = n + __popcll(b1 & below) + __popcll(b2 & below);
+                    if (ne >= 1) ent[pos] = (unsigned short)e0;
+                    if (ne == 2) ent[pos + 1] = (unsigned short)e1;
+                    n += __popcll(b1) + __popcll(b2);
+                }
+                const bool ar = __any(any_raw);
+                if (lane == 0) {
+                    sh_nent = n;
+                    sh_raw = ar;
+                }
+            }
+            __syncthreads();
+            const int nent = uniform_i(sh_nent);
+            const bool has_raw = uniform_i(sh_raw) != 0;
+
+            for (int eb = 0; eb < nent; eb += BE) {
+                const int ne = min(BE, nent - eb);
+                // ---- node photons: four lanes an entry, each a quarter of the
+                // column's samples in order
+                if (wv == 0 && has_raw) {
+                    // node offsets (entries that are not raw hold M nodes)
+                    int cnt = 0;
+                    if (lane < ne) {
+                        const unsigned en = ent[eb + lane];
+                        const int c = en & 127;
+                        cnt = (en & kEntRaw) ? kst[c + 1] - kst[c] : M;
+                    }
+                    int x = cnt;
+#pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const int y = __shfl_up(x, o);
+                        if (lane >= o) x += y;
+                    }
+                    if (lane < ne) noff[lane] = x - cnt;
+                    if (lane == ne - 1) noff[ne] = x;
+                }
+                {
+                    const int e = tid >> 2, part = tid & 3;
+                    unsigned en = kEntRaw;
+                    if (e < ne) en = ent[eb + e];
+                    const bool fit = !(en & kEntRaw);
+                    const int c = en & 127;
+                    double mu[M];
+#pragma unroll
+                    for (int p = 0; p < M; ++p) mu[p] = 0.0;
+                    if (fit) {
+                        // groups of four samples go round the quad's lanes, so a
+                        // quad reads 64 consecutive bytes
+                        const int ks = kst[c], ke = kst[c + 1];
+                        int k = ks + 4 * part;
+                        const double xi = (double)(X0 - H + c);
+                        const bool test = (en & kEntTest) != 0;
+                        const double ar = (double)((int)((en >> 7) & 63) - kMaxH + Y0);
+                        auto sample = [&](int kk, double phi) {
+                            const double t = fma((double)kk, dt, t0);
+                            const double y2 = 4.0 * (horner<DX>(cxr, t) - xi);
+                            if (test && floor(horner<DY>(cyr, t) + 0.5) != ar) phi = 0.0;
+                            double pa = phi, pb = 0.5 * y2 * phi;
+                            mu[0] += pa;
+                            mu[1] += pb;
+#pragma unroll
+                            for (int p = 2; p < M; ++p) {
+                                const double pc = fma(y2, pb, -pa);
+                                mu[p] += pc;
+                                pa = pb;
+                                pb = pc;
+                            }
+                        };
+                        // the next four values are loaded while these are added
+                        ST v[4], nv[4];
+                        if (k + 4 <= ke) Vec4<ST>::load(spec, k, v);
+                        for (; k + 4 <= ke; k += 16) {
+                            Vec4<ST>::load(spec, k + 20 <= ke ? k + 16 : k, nv);
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) sample(k + j, (double)v[j]);
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) v[j] = nv[j];
+                        }
+                        for (; k < ke; ++k) sample(k, (double)spec[k]);
+                    }
+#pragma unroll
+                    for (int p = 0; p < M; ++p) mu[p] = quad_sum(mu[p]);
+                    if (fit) {
+#pragma unroll
+                        for (int j = 0; j < (M + 3) / 4; ++j) {
+                            const int m = part + 4 * j;
+                            if (m >= M) break;
+                            // Clenshaw sum of mu_0 / 2 + sum_p mu_p T_p, times 2 / M
+                            const double xx = snode[m];
+                            double b1 = 0.0, b2 = 0.0;
+#pragma unroll
+                            for (int p = M - 1; p >= 1; --p) {
+                                const double b0 = fma(2.0 * xx, b1, mu[p] - b2);
+                                b2 = b1;
+                                b1 = b0;
+                            }
+                            const double sum = fma(xx, b1, 0.5 * mu[0] - b2);
+                            sphi[e][m] = (float)(sum * (2.0 / M) * (double)scale);
+                        }
+                    }
+                }
+                __syncthreads();
+                const int nn = has_raw ? uniform_i(noff[ne]) : ne * M;
+
+                // this thread's node and axis of a chunk: position from its anchor,
+                // sigma, photons (worked out one chunk ahead, beside the products)
+                float phi;
+                double pos, sgm;
+                int anchor;
+                auto prep = [&](int id) {
+                    phi = 0.0f;
+                    pos = 0.0;
+                    sgm = 1.0;
+                    anchor = 0;
+                    if (s >= CH || id >= nn) return;
+                    int e, m;
+                    if (has_raw) {
+                        int lo = 0, hi = ne - 1;  // last entry with noff <= id
+                        while (lo < hi) {
+                            const int mid = (lo + hi + 1) >> 1;
+                            if (noff[mid] <= id) lo = mid; else hi = mid - 1;
+                        }
+                        e = lo;
+                        m = id - noff[e];
+                    } else {
+                        e = id / M;
+                        m = id - e * M;
+                    }
+                    const unsigned en = ent[eb + e];
+                    const int c = en & 127;
+                    double x, y, ax, ay;
+                    if (en & kEntRaw) {
+                        const int k = kst[c] + m;
+                        const double t = fma((double)k, dt, t0);
+                        x = horner<DX>(cxr, t);
+                        y = horner<DY>(cyr, t);
+                        ax = floor(x + 0.5);
+                        ay = floor(y + 0.5);
+                        if (xaxis) phi = (float)spec_at(spec, k) * scale;
+                    } else {
+                        // t with x(t) = x by a chord and two Newton steps
+                        // from the column's first sample
+                        ax = (double)(X0 - H + c);
+                        x = fma(0.5, snode[m], ax);
+                        double t = fma((double)kst[c], dt, t0), dx;
+                        double xt = horner_d<DX>(cxr, t, &dx);
+                        double r = recip(dx);
+                        t = fma(x - xt, r, t);
+                        xt = horner_d<DX>(cxr, t, &dx);
+                        r = recip(dx);
+                        t = fma(x - xt, r, t);
+                        t = fma(x - horner<DX>(cxr, t), r, t);
+                        y = horner<DY>(cyr, t);
+                        ay = (double)((int)((en >> 7) & 63) - kMaxH + Y0);
+                        if (xaxis) phi = sphi[e][m];
+                    }
+                    pos = xaxis ? x - ax : y - ay;
+                    anchor = (int)(xaxis ? ax : ay);
+                    sgm = sigma_axis(F.sxy, F.gx, F.gy, F.gsx, F.gsy, x, y, xaxis ? 0 : 1);
+                };
+                prep(s);
+                for (int c0 = 0; c0 < nn; c0 += CH) {
+                    // ---- staging: this thread's node and axis
+                    {
+                        int nlo = 1, nhi = 0;
+                        const bool have = s < CH && c0 + s < nn;
+                        if (have) {
+                            if (xaxis)
+                                stage_axis<TX>(pos, sgm, H, (double)phi, anchor - H - X0, s, buf,
+                                               &nlo, &nhi);
+                            else
+                                stage_axis<TY>(pos, sgm, H, 1.0, anchor - H - Y0, s, ybuf, &nlo,
+                                               &nhi);
+                        }
+                        if (nlo > nhi) nlo = 1, nhi = 0;
+                        clear_lines(zlo, zhi, nlo, nhi, s, xaxis ? buf : ybuf);
+                        zlo = nlo;
+                        zhi = nhi;
+                        // the 16-line blocks that a group of 32 nodes reaches (none
+                        // where its photons are all 0), by ballots over the wave
+                        unsigned bits = block_bits(nlo, nhi);
+                        if (xaxis && phi == 0.0f) bits = 0u;
+                        unsigned ma = 0u, mb = 0u;  // nodes 0 .. 31 and 32 .. 63 of the wave
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const unsigned long long w = __ballot((bits >> q) & 1u);
+                            ma |= (unsigned)w != 0u ? 1u << q : 0u;
+                            mb |= (unsigned)(w >> 32) != 0u ? 1u << q : 0u;
+                        }
+                        if (lane < 2) smask[2 * (wv & 1) + lane][wv >> 1] = lane ? mb : ma;
+                    }
+                    __syncthreads();
+                    if (c0 + CH < nn) prep(c0 + CH + s);
+                    // ---- products: wave wv takes column block wv
+                    const float *const bx = buf + (16 * wv + l16) * LS + 4 * lg;
+                    const float *const ay = ybuf + l16 * LS + 4 * lg;
+                    // the chunk's last 8 nodes fill half a group of 16: the lanes
+                    // of its other half read the zeros behind the line
+                    const int last = CH - 8 + (lg > 2 ? -4 : 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const unsigned mx = (unsigned)uniform_i((int)smask[j][0]);
+                        const unsigned my = (unsigned)uniform_i((int)smask[j][1]);
+                        if (!((mx >> wv) & 1u) || my == 0u) continue;
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {  // 16 nodes: lane group lg holds 4 lg .. + 3
+                            const int g = j == 3 && h == 1 ? last : 32 * j + 16 * h;
+                            const f4 bv = *reinterpret_cast<const f4 *>(bx + g);
+#pragma unroll
+                            for (int rb = 0; rb < 2; ++rb) {
+                                if (!((my >> rb) & 1u)) continue;
+                                const f4 av = *reinterpret_cast<const f4 *>(ay + 16 * rb * LS + g);
+                                f4 part = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                                for (int q = 0; q < 4; ++q)
+                                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[q], part, 0, 0, 0);
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) acc[rb][q] += (double)part[q];
+                            }
+                        }
+                    }
+                    __syncthreads();
+                }
+            }
+        }
+        // wave wv holds column block wv: rows 4 q + lg of the FP64 product's
+        // register q, rows 4 lg + q of the others'
+        const int gx = X0 + 16 * wv + l16;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int gy = Y0 + 16 * rb + 4 * lg + q;
+                if (gx < F.nx && gy < F.ny)
+                    ((float *)F.out)[(size_t)gy * F.nx + gx] = (float)acc[rb][q];
+            }
+        __syncthreads();
+    }
+}
+
+template <int DX, int DY, typename ST>
+hipError_t launch_st(const FrameDev *frames_dev, int nodes, const int2 *work, int n_work,
+                     int *counter, int *err, int nb, hipStream_t s)
+{
+    if (nodes == 10)
+        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, 10>), dim3(nb), dim3(256), 0, s,
+                           frames_dev, work, n_work, counter, err);
+    else
+        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, 12>), dim3(nb), dim3(256), 0, s,
+                           frames_dev, work, n_work, counter, err);
+    return hipGetLastError();
+}
+
+template <int DX, int DY>
+hipError_t launch_deg(const FrameDev *frames_dev, const KernelCfg &cfg, const int2 *work,
+                      int n_work, int *counter, int *err, int nb, hipStream_t s)
+{
+    if (cfg.spec_f64)
+        return launch_st<DX, DY, double>(frames_dev, cfg.nodes, work, n_work, counter, err, nb, s);
+    return launch_st<DX, DY, float>(frames_dev, cfg.nodes, work, n_work, counter, err, nb, s);
+}
+
+}  // namespace
+
+hipError_t launch_sep_fit(const FrameDev *frames_dev, const KernelCfg &cfg, const int2 *work,
+                          int n_work, int *counter, int *err, hipStream_t s)
+{
+    // plain: one workgroup per tile; persistent: three per CU
+    const int nb = work == nullptr ? cfg.plain_tiles : (n_work < 768 ? n_work : 768);
+    if (nb <= 0) return hipSuccess;
+    if (cfg.degx <= 4 && cfg.degy <= 3)
+        return launch_deg<4, 3>(frames_dev, cfg, work, n_work, counter, err, nb, s);
+    return launch_deg<7, 7>(frames_dev, cfg, work, n_work, counter, err, nb, s);
+}
+
+}  // namespace e2e
