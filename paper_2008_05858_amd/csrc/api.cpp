@@ -720,6 +720,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         nodes[i] = sep_fit_nodes(fs[i], ps[i], prec, reqs[i].out_dtype);
         tile_geom(ps[i], prec, nodes[i], &tw, &th);
         int ntx = (fs[i]->nx + tw - 1) / tw, nty = (fs[i]->ny + th - 1) / th;
+        if (tr[i].chunk <= 0) tr[i].chunk = table_chunk(ntx * nty);
         tiles[i] = kind == E2E_PSF_TABLE ? table_units(ntx, nty, tr[i].chunk) : ntx * nty;
         seg_off[i] = seg_total;
         seg_total += (size_t)ntx * fs[i]->ntr;

@@ -96,7 +96,7 @@ struct Server;
 namespace e2e {
 // Launch choices of one workload shape, set by e2e_autotune.
 struct TuneRec {
-    int chunk = kTableChunk;  // table path: tiles per work unit
+    int chunk = 0;            // table path: tiles per work unit (0 = by the frame's size)
     int resident = 0;         // persistent launches: workgroups per CU (0 = default)
 };
 }  // namespace e2e

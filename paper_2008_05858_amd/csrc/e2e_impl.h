@@ -14,7 +14,7 @@ constexpr int kNCoef = 8;        // polynomial coefficients stored per axis
 constexpr int kOS = 4;           // PSF table cells per pixel on the GPU path
 constexpr int kTableThreads = 256;
 constexpr int kTableTH = 32;     // table-path tile height (rows)
-constexpr int kTableChunk = 8;   // default run of table-path tiles one workgroup walks
+constexpr int kTableChunk = 8;   // longest default run of table-path tiles one workgroup walks
 constexpr int kSepTile = 16;     // VALU separable / erf tile edge
 constexpr int kMfmaTW = 64;      // MFMA separable tile width (x)
 constexpr int kMfmaTH = 32;      // MFMA separable tile height (y)
@@ -113,6 +113,17 @@ enum : int {
 
 // Tile geometry of each path.
 inline int table_tw(int kw) { return (kTableThreads - kw) / kOS; }
+// Default run of a frame of `tiles` tiles.  A longer run shares each trace
+// segment's search, sums and stencil among more tiles, but leaves fewer
+// workgroups (768 fit the GPU, and several rounds of them are needed to even
+// out their uneven work).  Measured, run of 2 / 4 / 8 tiles: 512 x 452 (150
+// tiles) 0.13 / 0.19 / 0.23 ms; 2048^2 (2368) 0.20 / 0.26 / 0.36; 3000^2 (5076)
+// 0.28 / 0.33 / 0.39; 4096^2 (9472) 0.40 / 0.44 / 0.47 alone but 1.17 / 1.12 /
+// 1.15 as a batch of four and 2.10 / 1.97 / 1.91 of eight; 48-cell 6144^2
+// (22848) 10.6 / 9.7 / 10.4; 7500^2 (31490) 0.98 / 0.94 / 0.98; 9216^2 (47520)
+// 1.35 / 1.35 / 1.32.  It depends on the frame alone, so a frame has the same
+// bits alone and in a batch.
+inline int table_chunk(int tiles) { return tiles < 6144 ? 2 : tiles < 32768 ? 4 : kTableChunk; }
 // Work units of the table path: runs of `chunk` tiles down one column.
 inline int table_units(int ntx, int nty, int chunk) { return ntx * ((nty + chunk - 1) / chunk); }
 
