@@ -418,6 +418,7 @@ extern "C" e2e_status e2e_psf_load(e2e_ctx *ctx, const e2e_psf_desc *d, e2e_psf_
             sfq.push_back((float)(gw[q] * std::cos(th)));
         }
         P->sfi_R = (int)sfq.size() / 3;
+        P->smin[0] = P->smin[1] = smin;
         P->sfi_S = d->subpixels;
         P->sfi_shape = d->fiber_shape;
         P->rho = rho;
@@ -612,7 +613,7 @@ e2e_status e2e::validate_req(e2e_ctx *ctx, const e2e_render_req *r, FormatRes **
 static int sep_fit_nodes(const FormatRes *F, const PsfRes *P, int precision, int out_dtype)
 {
     if (P->kind != E2E_PSF_SEPARABLE || out_dtype != E2E_F32) return 0;
-    if (F->ntr > kSepFitMaxTraces || F->bend > 1e-2) return 0;
+    if (F->ntr > kListTraces || F->bend > 1e-2) return 0;
     const int tiles = ((F->nx + kMfmaTW - 1) / kMfmaTW) * ((F->ny + kMfmaTH - 1) / kMfmaTH);
     const bool few = tiles < kSepFitTiles;
     const double dense = precision == E2E_PREC_F64   ? (few ? 22.0 : 6.0)
@@ -631,9 +632,18 @@ static int sep_fit_nodes(const FormatRes *F, const PsfRes *P, int precision, int
     return 0;
 }
 
+// Explicit fiber images of FP32 frames by k_sfi_terms.hip (1) or one by one
+// (0).  Its sub-pixel series fall as (1 / 2 sigma)^2k: eight terms leave 1e-9
+// of the peak at sigma = 0.58 px.  FP64 frames keep k_sfi.hip's own rounding.
+static int sfi_terms(const FormatRes *F, const PsfRes *P, int out_dtype)
+{
+    return P->kind == E2E_PSF_SFI && out_dtype == E2E_F32 && F->ntr <= kListTraces &&
+           std::min(P->smin[0], P->smin[1]) >= 0.58;
+}
+
 static void tile_geom(const PsfRes *P, int precision, int nodes, int *tw, int *th)
 {
-    if (nodes > 0) {
+    if (P->kind == E2E_PSF_SEPARABLE && nodes > 0) {
         *tw = kMfmaTW;
         *th = kMfmaTH;
     } else if (P->kind == E2E_PSF_TABLE) {
@@ -717,7 +727,8 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
     size_t temp_bytes = 0;
     for (int i = 0; i < n; ++i) {
         int tw, th;
-        nodes[i] = sep_fit_nodes(fs[i], ps[i], prec, reqs[i].out_dtype);
+        nodes[i] = kind == E2E_PSF_SFI ? sfi_terms(fs[i], ps[i], reqs[i].out_dtype)
+                                       : sep_fit_nodes(fs[i], ps[i], prec, reqs[i].out_dtype);
         tile_geom(ps[i], prec, nodes[i], &tw, &th);
         int ntx = (fs[i]->nx + tw - 1) / tw, nty = (fs[i]->ny + th - 1) / th;
         if (tr[i].chunk <= 0) tr[i].chunk = table_chunk(ntx * nty);
@@ -854,7 +865,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
     // work list: frames by decreasing size, tiles in order
     sc->h_work.clear();
     // the frames of one launch share a kernel: work items [w0, w1) of each
-    // node count present (separable frames; other kinds have one group)
+    // node count present (0, 10 and 12 for separable frames, 0 and 1 for SFI ones)
     struct Group {
         int nodes;
         size_t w0, w1;
@@ -870,7 +881,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         // frames of equal size go unit by unit, so the same unit of each (the
         // same spectrum ranges, read again under another Doppler shift) runs
         // at about the same time and its reads hit the caches
-        for (int nn : {0, 10, 12}) {
+        for (int nn : {0, 1, 10, 12}) {
             std::vector<int> own;
             for (int i : order)
                 if (nodes[i] == nn) own.push_back(i);
@@ -956,6 +967,8 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
             prof_begin(ctx, s, name);
             if (kind == E2E_PSF_TABLE)
                 q = launch_table(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
+            else if (kind == E2E_PSF_SFI && kc.nodes > 0)
+                q = launch_sfi_terms(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
             else if (kc.nodes > 0)
                 q = launch_sep_fit(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
             else if (kind == E2E_PSF_SEPARABLE && mfma)

@@ -34,7 +34,7 @@ struct PsfRes {
     int H = 0, gx = 1, gy = 1, kw = 0, kh = 0, os = 0;
     uint16_t *tfrag = nullptr;  // table taps as fp16 hi/lo product fragments
     float *sxy = nullptr;   // separable sigma grid
-    double smin[2] = {0, 0};  // separable: smallest sigma_x, sigma_y of the grid
+    double smin[2] = {0, 0};  // separable: smallest sigma_x, sigma_y of the grid (SFI: of both)
     double sstep[2] = {0, 0}; // separable: largest sigma step between nodes along x, y
     float *sfq = nullptr;   // SFI: quadrature nodes [R][3]
     int sfi_R = 0, sfi_S = 0, sfi_shape = 0;

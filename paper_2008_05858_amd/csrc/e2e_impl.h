@@ -19,7 +19,7 @@ constexpr int kSepTile = 16;     // VALU separable / erf tile edge
 constexpr int kMfmaTW = 64;      // MFMA separable tile width (x)
 constexpr int kMfmaTH = 32;      // MFMA separable tile height (y)
 constexpr int kMaxTileTraces = 512;
-constexpr int kSepFitMaxTraces = 65535;  // traces of a frame the node path lists in 16 bits
+constexpr int kListTraces = 65535;   // traces of a frame that a tile's 16-bit list can name
 constexpr int kSepFitTiles = 768;   // tiles of a frame that fill the node path's workgroups
 constexpr int kCounters = 3;     // work-queue counters: one per render kernel of a batch
 constexpr int kSfiMaxR = 16;     // SFI: quadrature node pairs (32 nodes)
@@ -134,7 +134,8 @@ struct KernelCfg {
     int spec_f64;       // spectra element type
     int plain_tiles;    // plain launch: tiles of frame 0 (one block each)
     int precision;      // E2E_PREC_*
-    int nodes;          // separable FP32 frames: nodes a pixel column (0: per sample)
+    int nodes;          // separable: nodes a pixel column; SFI: 1 = product of terms;
+                        // 0 = the per-sample kernels
     int resident;       // persistent launches: workgroups per CU (0 = path default)
 };
 
@@ -153,6 +154,8 @@ hipError_t launch_sep_mfma(const FrameDev *frames_dev, const KernelCfg &cfg, con
                            int n_work, int *counter, int *err, hipStream_t s);
 hipError_t launch_sep_fit(const FrameDev *frames_dev, const KernelCfg &cfg, const int2 *work,
                           int n_work, int *counter, int *err, hipStream_t s);
+hipError_t launch_sfi_terms(const FrameDev *frames_dev, const KernelCfg &cfg, const int2 *work,
+                            int n_work, int *counter, int *err, hipStream_t s);
 hipError_t launch_noise(void *frame, int f64, int64_t n, uint64_t seed, uint32_t frame_index,
                         hipStream_t s);
 hipError_t launch_noise_frames(const FrameDev *frames_dev, const FrameDev *frames_host,

@@ -48,19 +48,16 @@
 // recurrence); the Gaussian runs along the window by two multiplications a
 // pixel.  Eight terms leave an absolute error below 4e-10 for sigma >= 0.58.
 // The order of every sum is fixed: the result is deterministic.
-#include "psf_gauss.h"
+#include "sep_stage.h"
 
 namespace e2e {
 
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int TX = kMfmaTW;            // 64 columns = 4 blocks of 16, one per wave
 constexpr int TY = kMfmaTH;            // 32 rows = 2 blocks of 16
-constexpr int CH = 120;                // nodes per chunk (12 columns of 10, 10 of 12)
-constexpr int LS = CH + 4;             // floats of a line in LDS, see lds_at
 constexpr int NCOL = TX + 2 * kMaxH;   // pixel columns whose samples reach the tile
 constexpr int NENT = 2 * NCOL;         // list entries: at most two row anchors a column
 
@@ -79,43 +76,6 @@ constexpr unsigned kEntTest = 1u << 13;  // only the samples with this row ancho
 __device__ __forceinline__ unsigned ent_pack(int col, int arow)
 {
     return (unsigned)col | ((unsigned)(arow + kMaxH) << 7);
-}
-
-// Float index of (pixel line p, node s): the operands of one chunk in LDS are
-// [line][node] FP32 weights, four floats of zeros after each line.  Lines are
-// 124 floats apart, so the 16 lines that a fragment read touches start on
-// different banks and a thread's writes go down the lines at a fixed step.
-__device__ __forceinline__ int lds_at(int p, int s) { return p * LS + s; }
-
-// 1 / v for v > 0: the hardware reciprocal and two Newton steps
-__device__ __forceinline__ double recip(double v)
-{
-    double r = __builtin_amdgcn_rcp(v);
-    r = fma(r, fma(-v, r, 1.0), r);
-    return fma(r, fma(-v, r, 1.0), r);
-}
-
-// exp(x) for x in [-0.4, 0]: Taylor to x^9 (truncation below 3e-11)
-__device__ __forceinline__ double exp_small(double x)
-{
-    double p = fma(x, 1.0 / 362880.0, 1.0 / 40320.0);
-    p = fma(p, x, 1.0 / 5040.0);
-    p = fma(p, x, 1.0 / 720.0);
-    p = fma(p, x, 1.0 / 120.0);
-    p = fma(p, x, 1.0 / 24.0);
-    p = fma(p, x, 1.0 / 6.0);
-    p = fma(p, x, 0.5);
-    p = fma(p, x, 1.0);
-    return fma(p, x, 1.0);
-}
-
-// exp(x) for |x| < 700: 2^n times exp of the remainder, |r| <= ln2 / 2
-// (Taylor to r^9, relative error below 1e-11)
-__device__ __forceinline__ double exp_mid(double x)
-{
-    const double n = rint(x * 1.4426950408889634);
-    const double r = fma(n, -0.6931471805599453, x);
-    return ldexp(exp_small(r), (int)n);
 }
 
 // Pixel integrals of one Gaussian (sigma sg, centre d from the anchor pixel)
@@ -194,25 +154,6 @@ __device__ __forceinline__ void stage_axis(double d, double sg, int H, double sc
     }
 }
 
-// zero lines [zlo, zhi] of sample slot s except [nlo, nhi]
-__device__ __forceinline__ void clear_lines(int zlo, int zhi, int nlo, int nhi, int s,
-                                            float *b)
-{
-    const bool none = nlo > nhi;
-    const int e1 = none ? zhi : min(zhi, nlo - 1);
-    for (int p = zlo; p <= e1; ++p) b[lds_at(p, s)] = 0.0f;
-    if (!none)
-        for (int p = max(zlo, nhi + 1); p <= zhi; ++p) b[lds_at(p, s)] = 0.0f;
-}
-
-// 16-line blocks covered by lines [lo, hi]
-__device__ __forceinline__ unsigned block_bits(int lo, int hi)
-{
-    if (lo > hi) return 0u;
-    const int b0 = lo >> 4, b1 = hi >> 4;
-    return ((2u << b1) - 1u) & ~((1u << b0) - 1u);
-}
-
 // One axis' sigma of a sample, bilinear in the field over the node grid.
 __device__ __forceinline__ double sigma_axis(const float *sxy, int gx, int gy, double gsx,
                                              double gsy, double x, double y, int c)
@@ -270,7 +211,6 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
 {
     constexpr int BE = M == 10 ? 60 : 50;   // list entries per batch (4 lanes each)
     static_assert(TX == 64 && TY == 32 && CH == 120, "block geometry");
-    static_assert((TX + TY) * LS % 4 == 0, "zeroed by 16-byte words");
     static_assert(NCOL <= 128 && TY + 2 * kMaxH < 64, "entry fields");
     __shared__ __attribute__((aligned(16))) float buf[(TX + TY) * LS];
     __shared__ float sphi[BE][M];           // node photons of the batch
@@ -313,38 +253,8 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
         const int X0 = tx * TX, Y0 = ty * TY;
         const int ncol = min(TX, F.nx - X0) + 2 * H;
         const SegDev *segs = F.segs + (size_t)tx * ntr;
-        // ---- traces that reach the tile, ascending: 256 tested at a time
-        int count = 0;
-        for (int base = 0; base < ntr; base += 256) {
-            const int tr = base + tid;
-            bool ok = false;
-            if (tr < ntr) {
-                const SegDev sv = segs[tr];
-                ok = sv.k0 < sv.k1 && sv.ty0 <= ty && ty <= sv.ty1;
-            }
-            const unsigned long long m = __ballot(ok);
-            const int par = (base >> 8) & 1;  // two sets of counts: one barrier a turn
-            if (lane == 0) smask[wv][par] = (unsigned)__popcll(m);
-            __syncthreads();
-            int pos = count + __popcll(m & ((1ull << lane) - 1ull));
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const int v = (int)smask[w][par];
-                pos += w < wv ? v : 0;
-                count += v;
-            }
-            if (ok) {
-                if (pos < kMaxTileTraces) tlist[pos] = (unsigned short)tr;
-                else atomicOr(err, kErrTileTraces);
-            }
-        }
-        count = uniform_i(min(count, kMaxTileTraces));
-        // the staging planes start at zero
-        {
-            const uint4 zz = {0u, 0u, 0u, 0u};
-            uint4 *b4 = reinterpret_cast<uint4 *>(buf);
-            for (int q = tid; q < (TX + TY) * LS / 4; q += 256) b4[q] = zz;
-        }
+        int count = tile_traces(segs, ntr, ty, tid, smask, tlist, err);
+        zero_lines(buf, tid);
         __syncthreads();
         int zlo = 1, zhi = 0;  // lines this thread's node slot holds (none)
         double acc[2][4];
@@ -364,7 +274,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
             for (int j = 0; j <= DY; ++j) cyr[j] = T.cy[j];
             const TraceFrameDev &TF = F.tf[tr];
             const double t0 = TF.t0, dt = TF.dt;
-            const float scale = (float)TF.scale;
+            const double scale = TF.scale;
             const ST *spec = (const ST *)TF.spec;
             const int nsamp = T.n;
 
@@ -562,7 +472,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                                 b1 = b0;
                             }
                             const double sum = fma(xx, b1, 0.5 * mu[0] - b2);
-                            sphi[e][m] = (float)(sum * (2.0 / M) * (double)scale);
+                            sphi[e][m] = (float)(sum * (2.0 / M) * scale);
                         }
                     }
                 }
@@ -603,7 +513,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                         y = horner<DY>(cyr, t);
                         ax = floor(x + 0.5);
                         ay = floor(y + 0.5);
-                        if (xaxis) phi = (float)spec_at(spec, k) * scale;
+                        if (xaxis) phi = (float)(spec_at(spec, k) * scale);
                     } else {
                         // t with x(t) = x by a chord and two Newton steps
                         // from the column's first sample
@@ -643,64 +553,18 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                         clear_lines(zlo, zhi, nlo, nhi, s, xaxis ? buf : ybuf);
                         zlo = nlo;
                         zhi = nhi;
-                        // the 16-line blocks that a group of 32 nodes reaches (none
-                        // where its photons are all 0), by ballots over the wave
-                        unsigned bits = block_bits(nlo, nhi);
-                        if (xaxis && phi == 0.0f) bits = 0u;
-                        unsigned ma = 0u, mb = 0u;  // nodes 0 .. 31 and 32 .. 63 of the wave
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const unsigned long long w = __ballot((bits >> q) & 1u);
-                            ma |= (unsigned)w != 0u ? 1u << q : 0u;
-                            mb |= (unsigned)(w >> 32) != 0u ? 1u << q : 0u;
-                        }
-                        if (lane < 2) smask[2 * (wv & 1) + lane][wv >> 1] = lane ? mb : ma;
+                        // (a node without photons reaches none)
+                        group_masks(xaxis && phi == 0.0f ? 0u : block_bits(nlo, nhi), lane, wv, smask);
                     }
                     __syncthreads();
                     if (c0 + CH < nn) prep(c0 + CH + s);
                     // ---- products: wave wv takes column block wv
-                    const float *const bx = buf + (16 * wv + l16) * LS + 4 * lg;
-                    const float *const ay = ybuf + l16 * LS + 4 * lg;
-                    // the chunk's last 8 nodes fill half a group of 16: the lanes
-                    // of its other half read the zeros behind the line
-                    const int last = CH - 8 + (lg > 2 ? -4 : 0);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const unsigned mx = (unsigned)uniform_i((int)smask[j][0]);
-                        const unsigned my = (unsigned)uniform_i((int)smask[j][1]);
-                        if (!((mx >> wv) & 1u) || my == 0u) continue;
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {  // 16 nodes: lane group lg holds 4 lg .. + 3
-                            const int g = j == 3 && h == 1 ? last : 32 * j + 16 * h;
-                            const f4 bv = *reinterpret_cast<const f4 *>(bx + g);
-#pragma unroll
-                            for (int rb = 0; rb < 2; ++rb) {
-                                if (!((my >> rb) & 1u)) continue;
-                                const f4 av = *reinterpret_cast<const f4 *>(ay + 16 * rb * LS + g);
-                                f4 part = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                                for (int q = 0; q < 4; ++q)
-                                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[q], part, 0, 0, 0);
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) acc[rb][q] += (double)part[q];
-                            }
-                        }
-                    }
+                    tile_products<false>(buf, ybuf, nullptr, smask, wv, l16, lg, acc);
                     __syncthreads();
                 }
             }
         }
-        // wave wv holds column block wv: rows 4 q + lg of the FP64 product's
-        // register q, rows 4 lg + q of the others'
-        const int gx = X0 + 16 * wv + l16;
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int gy = Y0 + 16 * rb + 4 * lg + q;
-                if (gx < F.nx && gy < F.ny)
-                    ((float *)F.out)[(size_t)gy * F.nx + gx] = (float)acc[rb][q];
-            }
+        put_tile(F, X0, Y0, wv, l16, lg, acc);
         __syncthreads();
     }
 }
