@@ -3,6 +3,8 @@
 // smoothing widths, launches, and the parabola vertex of the summed CCF.
 #include <cmath>
 #include <cstring>
+#include <map>
+#include <tuple>
 #include <vector>
 
 #include "api_internal.h"
@@ -10,14 +12,24 @@
 namespace e2e {
 hipError_t launch_extract(const TraceDev *trs, int ntr, int nx, int ny, const void *frame,
                           int f64, double A, double *flux, double *edges, hipStream_t s);
-hipError_t launch_smooth3(const void *lt_dev, int ntr, int64_t nmax, int wmax, int f64,
+hipError_t launch_smooth3(const void *lt_dev, int n_tmpl, int64_t nmax, int wmax, int f64,
                           hipStream_t s);
 int loop_max_width();
-hipError_t launch_ccf(const TraceDev *trs, int tr0, int ntr, const void *lt_dev, int nx,
-                      const double *flux, const double *flat, const double *edges, double v0,
-                      double dv, int nv, double *C, hipStream_t s);
+bool loop_needs_p(int w);
+int ccf_runs(int nx, int ntr);
+hipError_t launch_ccf_mean(const TraceDev *trs, const void *tl_dev, int n_tr, const void *lt_dev,
+                           int nx, const double *flux, const double *flat, const double *edges,
+                           double v0, double dv, int nv, double *mean, hipStream_t s);
+hipError_t launch_ccf(const TraceDev *trs, const void *tl_dev, int n_tr, int ntr, const void *lt_dev,
+                      int nx, double spp, double vspan, const double *flux, const double *flat,
+                      const double *edges, double v0, double dv, int nv, const double *mean,
+                      double *part, hipStream_t s);
+hipError_t launch_ccf_sum(const double *part, int ntr, int nx, int nv, double *C, double *tot,
+                          hipStream_t s);
+size_t loop_template_bytes();
 size_t loop_trace_bytes();
-void loop_trace_fill(void *dst, const void *tmpl, double *P, double *X, int64_t n, int w);
+void loop_template_fill(void *dst, const void *tmpl, double *P, double *X, int64_t n, int w);
+void loop_trace_fill(void *dst, int trace, int tmpl);
 }  // namespace e2e
 
 using namespace e2e;
@@ -172,10 +184,12 @@ extern "C" e2e_status e2e_ccf(e2e_ctx *ctx, e2e_format_id fmt, const e2e_ccf_req
     // moving-mean width of each trace: the odd integer nearest sqrt(4 s^2 + 1),
     // s = smooth_px samples-per-pixel
     std::vector<int> w(ntr);
+    std::vector<double> spans(ntr);
     int64_t nmax = 0;
     for (int t = 0; t < ntr; ++t) {
         const TraceDev &T = F->host[t];
         const double span = horner_host(T.cx, kNCoef - 1, 1.0) - horner_host(T.cx, kNCoef - 1, -1.0);
+        spans[t] = span;
         const double sg = r->smooth_px * (double)T.n / span;
         int wi = (int)std::floor(std::sqrt(4.0 * sg * sg + 1.0) + 0.5);
         if (wi % 2 == 0) wi += 1;
@@ -185,59 +199,97 @@ extern "C" e2e_status e2e_ccf(e2e_ctx *ctx, e2e_format_id fmt, const e2e_ccf_req
                         t, w[t], loop_max_width());
         nmax = std::max<int64_t>(nmax, T.n);
     }
-    double *Cd;
-    {
-        void *c;
-        if ((e = B.get(&c, (size_t)ntr * nv * 8)) != hipSuccess) return hip_fail(e, "ccf out");
-        Cd = (double *)c;
+    // templates to smooth: one for each (spectrum slot, length, width) in use;
+    // the slices of a fiber share theirs.  tmpl_of[t]: that of trace t.
+    struct Tmpl {
+        int slot, w;
+        int64_t n;
+        std::vector<int> traces;
+    };
+    std::vector<Tmpl> uniq;
+    std::map<std::tuple<int, int, int64_t>, int> seen;
+    for (int t = 0; t < ntr; ++t) {
+        const TraceDev &T = F->host[t];
+        auto it = seen.emplace(std::make_tuple(T.slot, w[t], (int64_t)T.n), (int)uniq.size());
+        if (it.second) uniq.push_back({T.slot, w[t], T.n, {}});
+        uniq[it.first->second].traces.push_back(t);
     }
-    // traces in groups: smoothed templates (X) and prefix sums (P) per trace
-    const int G = 64;
-    void *work, *ltd;
-    if ((e = B.get(&work, (size_t)std::min(G, ntr) * (2 * nmax + 2) * 8)) != hipSuccess)
-        return hip_fail(e, "template scratch");
-    const size_t ltb = loop_trace_bytes();
-    if ((e = B.get(&ltd, (size_t)G * ltb)) != hipSuccess) return hip_fail(e, "trace table");
-    void *stage = nullptr;
-    if ((e = hipHostMalloc(&stage, (size_t)G * ltb)) != hipSuccess) return hip_fail(e, "staging");
-    for (int t0 = 0; t0 < ntr && e == hipSuccess; t0 += G) {
-        const int g = std::min(G, ntr - t0);
-        // the previous group's table copy must have been consumed
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) break;
-        for (int q = 0; q < g; ++q) {
-            const TraceDev &T = F->host[t0 + q];
-            double *base = (double *)work + (size_t)q * (2 * nmax + 2);
-            loop_trace_fill((char *)stage + q * ltb, tmpl[T.slot], base, base + nmax + 1, T.n,
-                            w[t0 + q]);
-        }
-        if ((e = hipMemcpyAsync(ltd, stage, g * ltb, hipMemcpyHostToDevice, s)) != hipSuccess)
-            break;
-        prof_begin(ctx, s, "template_smooth");
+    // as many at a time as 192 MB of smoothed samples hold (they stay in the
+    // memory-side cache between the two kernels), and all the tables in one upload
+    bool wide = false;
+    for (auto &u : uniq) wide |= loop_needs_p(u.w);
+    const size_t half = ((size_t)nmax + 1) & ~(size_t)1;  // even: the CCF loads 16 bytes
+    const size_t stride = half * (wide ? 2 : 1);
+    const int nu = (int)uniq.size();
+    const int G = (int)std::max<size_t>(1, std::min<size_t>(nu, ((size_t)192 << 20) / (stride * 8)));
+    auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    const size_t b_tm = up(nu * loop_template_bytes()), b_tl = up(ntr * loop_trace_bytes());
+    const size_t b_mean = up((size_t)ntr * 8), b_tot = up((size_t)nv * 8);
+    const size_t b_C = up((size_t)ntr * nv * 8), b_part = up((size_t)ntr * ccf_runs(nx, ntr) * nv * 8);
+    char *ws;
+    {
+        void *p;
+        if ((e = B.get(&p, b_tm + b_tl + b_mean + b_tot + b_C + b_part + G * stride * 8)) != hipSuccess)
+            return hip_fail(e, "ccf workspace");
+        ws = (char *)p;
+    }
+    char *const tm = ws, *const tl = tm + b_tm;
+    double *const mean = (double *)(tl + b_tl), *const tot_d = (double *)(tl + b_tl + b_mean);
+    double *const Cd = (double *)((char *)tot_d + b_tot), *const part = (double *)((char *)Cd + b_C);
+    double *const work = (double *)((char *)part + b_part);
+    std::vector<char> table(b_tm + b_tl);
+    int at = 0;
+    for (int u = 0; u < nu; ++u) {
+        double *base = work + (size_t)(u % G) * stride;
+        loop_template_fill(table.data() + u * loop_template_bytes(), tmpl[uniq[u].slot], base + half, base,
+                           uniq[u].n, uniq[u].w);
+        for (int t : uniq[u].traces) loop_trace_fill(table.data() + b_tm + at++ * loop_trace_bytes(), t, u);
+    }
+    e = hipMemcpyAsync(tm, table.data(), table.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) {
+        prof_begin(ctx, s, "ccf");
+        e = launch_ccf_mean(F->dev, tl, ntr, tm, nx, fd, fl, ld, r->v0_mps, r->dv_mps, nv, mean, s);
+        prof_end(ctx, s);
+    }
+    at = 0;
+    for (int u0 = 0; u0 < nu && e == hipSuccess; u0 += G) {
+        const int g = std::min(G, nu - u0);
         int64_t ng = 0;
-        int wg = 1;
-        for (int q = 0; q < g; ++q) {
-            ng = std::max<int64_t>(ng, F->host[t0 + q].n);
-            wg = std::max(wg, w[t0 + q]);
+        int wg = 1, nt = 0;
+        double spp = 0.0, vspan = 0.0;  // samples a column, samples the velocities span
+        for (int u = u0; u < u0 + g; ++u) {
+            ng = std::max(ng, uniq[u].n);
+            wg = std::max(wg, uniq[u].w);
+            nt += (int)uniq[u].traces.size();
+            for (int t : uniq[u].traces) {
+                const TraceDev &T = F->host[t];
+                spp = std::max(spp, 1.1 * (double)T.n / spans[t]);
+                vspan = std::max(vspan, (nv - 1) * std::fabs(r->dv_mps) / 299792458.0 * T.lmax *
+                                            (double)T.n / (T.lmax - T.lmin));
+            }
         }
-        e = launch_smooth3(ltd, g, ng, wg, r->template_dtype == E2E_F64, s);
+        prof_begin(ctx, s, "template_smooth");
+        e = launch_smooth3(tm + u0 * loop_template_bytes(), g, ng, wg, r->template_dtype == E2E_F64, s);
         prof_end(ctx, s);
         if (e != hipSuccess) break;
         prof_begin(ctx, s, "ccf");
-        e = launch_ccf(F->dev, t0, g, ltd, nx, fd, fl, ld, r->v0_mps, r->dv_mps, nv, Cd, s);
+        e = launch_ccf(F->dev, tl + at * loop_trace_bytes(), nt, ntr, tm, nx, spp, vspan, fd, fl, ld,
+                       r->v0_mps, r->dv_mps, nv, mean, part, s);
         prof_end(ctx, s);
+        at += nt;
     }
-    std::vector<double> C((size_t)ntr * nv);
-    if (e == hipSuccess) e = hipMemcpyAsync(C.data(), Cd, C.size() * 8, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess && r->ccf_out)
-        e = hipMemcpyAsync(r->ccf_out, Cd, C.size() * 8,
-                           r->on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    hipHostFree(stage);
+    // the sums over the columns' runs and over the traces, each in order
+    double *const Cout = r->ccf_out && r->on_device ? r->ccf_out : Cd;
+    if (e == hipSuccess) e = launch_ccf_sum(part, ntr, nx, nv, Cout, tot_d, s);
+    std::vector<double> tot(nv);
+    if (e == hipSuccess) e = hipMemcpyAsync(tot.data(), tot_d, nv * 8, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess && r->ccf_out && !r->on_device)
+        e = hipMemcpyAsync(r->ccf_out, Cd, (size_t)ntr * nv * 8, hipMemcpyDeviceToHost, s);
+    // (also before an error return: the upload reads `table` until it is done)
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
     if (e != hipSuccess) return hip_fail(e, "e2e_ccf");
-    // parabola vertex of the summed CCF (traces added in order)
-    std::vector<double> tot(nv, 0.0);
-    for (int t = 0; t < ntr; ++t)
-        for (int k = 0; k < nv; ++k) tot[k] += C[(size_t)t * nv + k];
+    // parabola vertex of the summed CCF
     int kb = 1;
     for (int k = 1; k < nv - 1; ++k)
         if (tot[k] > tot[kb]) kb = k;

@@ -8,17 +8,17 @@
 //    on x(t) (FP64), the edge wavelength, and the column's box extraction
 //    over the rows within +-A of the trace centre (fractional end rows).
 //    Neighbouring lanes read neighbouring pixels of each row.
-//  * k_smooth3_fused / k_box_pass: the three passes of a clipped moving
-//    mean over the template (the input spectrum of the trace); one
-//    workgroup per 2048 outputs of a trace stages its inputs and the
-//    windows around them in LDS, scans them (FP64) and takes window
-//    differences -- all three passes in one launch when the window is
-//    narrow (the template read once, the result written once), else one
-//    launch per pass.
-//  * k_ccf: one workgroup per (trace, 8 trial velocities): the mean of the
-//    flat-divided flux over the usable columns, then per column and
-//    velocity the template read at the Doppler-shifted column centre by
-//    linear interpolation; fixed-order block sums.
+//  * k_smooth3 / k_box_pass: the three passes of a clipped moving mean over a
+//    template (the input spectrum of a trace): all three in one launch while
+//    the window is narrow, from registers and one LDS array of prefix sums,
+//    else one launch per pass.  Traces that share a template and a width (the
+//    slices of a fiber) share its smoothed copy.
+//  * k_ccf_mean / k_ccf / k_ccf_sum: the mean of the flat-divided flux over
+//    the usable columns; then a workgroup per (trace, run of columns) stages
+//    the stretch of the smoothed template that a few columns read under every
+//    trial velocity in LDS and adds up all velocities from there (linear
+//    interpolation at the Doppler-shifted column centre); fixed-order sums
+//    over the workgroups, and over the traces.
 #include "dev_common.h"
 
 namespace e2e {
@@ -80,17 +80,22 @@ __global__ __launch_bounds__(256) void k_extract(const TraceDev *__restrict__ tr
     flux[(size_t)tr * nx + i] = acc;
 }
 
-// Per-trace parameters of the template smoothing and the CCF.
-struct LoopTrace {
-    const void *tmpl;   // template (spectrum slot), FP32 or FP64
-    double *P;          // prefix sums, n + 1
+// A template to smooth.
+struct LoopTemplate {
+    const void *tmpl;   // spectrum slot, FP32 or FP64
+    double *P;          // between the passes of a wide window, n values
     double *X;          // smoothed template, n
     int64_t n;
     int32_t w;          // moving-mean width (odd)
     int32_t pad;
 };
 
-constexpr int SMT = 2048;        // smoothed samples per workgroup
+// A trace of the CCF: its number and its smoothed template's.
+struct LoopTrace {
+    int32_t trace, tmpl;
+};
+
+constexpr int SMT = 2048;        // smoothed samples per workgroup (one pass)
 constexpr int SMW = 4095;        // widest moving mean
 
 __device__ void lds_scan(double *q, int len, double *tsum)
@@ -127,11 +132,11 @@ __device__ void lds_scan(double *q, int len, double *tsum)
 // window clipped to the array) over its count.  Pass 0 reads the template
 // into X, pass 1 X into P, pass 2 P into X.
 template <typename TT>
-__global__ __launch_bounds__(256) void k_box_pass(const LoopTrace *__restrict__ lt, int pass)
+__global__ __launch_bounds__(256) void k_box_pass(const LoopTemplate *__restrict__ lt, int pass)
 {
     __shared__ double q[SMT + SMW + 1];
     __shared__ double tsum[4];
-    const LoopTrace L = lt[blockIdx.y];
+    const LoopTemplate L = lt[blockIdx.y];
     const int64_t n = L.n, h = L.w / 2;
     const int64_t t0 = (int64_t)blockIdx.x * SMT;
     if (t0 >= n) return;
@@ -152,88 +157,152 @@ __global__ __launch_bounds__(256) void k_box_pass(const LoopTrace *__restrict__ 
     }
 }
 
-// All three passes in one launch when the windows are narrow (6h <= SMT):
-// a workgroup loads its SMT outputs with 3h on each side, and pass k
-// (k = 1, 2, 3) produces the range widened by (3 - k) h from the previous
-// one in LDS (scan, window differences).  The template is read once and the
-// smoothed template written once; the halo is recomputed by the neighbours.
-constexpr int SFH = SMT / 6;     // widest half-window of the fused form
+// All three passes in one launch.  A workgroup covers SL consecutive samples,
+// its outputs and 3h on each side (clipped to the template); each thread keeps
+// a run of SR of them in registers through the passes.  A pass scans the runs
+// (registers, wave shuffles, the four wave totals), writes the exclusive prefix
+// sums to LDS, and takes each output as the difference of two of them; the
+// range that holds valid values shrinks by h a side each time.  SR is odd, so
+// the 64-bit reads and writes of a wave fall on distinct banks.  The version
+// before this one scanned in LDS, a run of 12 values a thread (eight lanes to a
+// bank) and divided every output: 64 templates of 1e6 samples, w = 279,
+// 765 us; this one 0.34 ms for as many (2.3 TB/s).
+constexpr int STH = 512, SR = 9, SL = STH * SR;
+constexpr int SFH = 512;         // widest half-window: at least SL - 6 * 512 = 1536 outputs
 
 template <typename TT>
-__global__ __launch_bounds__(256) void k_smooth3_fused(const LoopTrace *__restrict__ lt)
+__global__ __launch_bounds__(STH) void k_smooth3(const LoopTemplate *__restrict__ lt, int outs)
 {
-    __shared__ double qa[SMT + 6 * SFH + 2], qb[SMT + 6 * SFH + 2];
-    __shared__ double tsum[4];
-    const LoopTrace L = lt[blockIdx.y];
+    __shared__ double q[SL + 1];
+    __shared__ double tsum[STH / 64];
+    const LoopTemplate L = lt[blockIdx.y];
     const int64_t n = L.n, h = L.w / 2;
-    const int64_t t0 = (int64_t)blockIdx.x * SMT;
+    const int64_t t0 = (int64_t)blockIdx.x * outs;
     if (t0 >= n) return;
-    const int64_t t1 = t0 + SMT < n ? t0 + SMT : n;
-    const int tid = threadIdx.x;
-    int64_t b = t0 - 3 * h > 0 ? t0 - 3 * h : 0, e = t1 + 3 * h < n ? t1 + 3 * h : n;
-    int len = (int)(e - b);
-    for (int k = tid; k < len; k += 256) qa[k + 1] = (double)((const TT *)L.tmpl)[b + k];
-    if (tid == 0) qa[0] = 0.0;
+    const int64_t t1 = t0 + outs < n ? t0 + outs : n;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t b = t0 - 3 * h > 0 ? t0 - 3 * h : 0, e = t1 + 3 * h < n ? t1 + 3 * h : n;
+    const int len = (int)(e - b);
+    for (int k = tid; k < SL; k += STH) q[k] = k < len ? (double)((const TT *)L.tmpl)[b + k] : 0.0;
     __syncthreads();
-    double *src = qa, *dst = qb;
+    double v[SR];
+    const int i0 = tid * SR;
+#pragma unroll
+    for (int j = 0; j < SR; ++j) v[j] = q[i0 + j];
+    const bool clipped = t0 < 3 * h || t1 + 3 * h > n;
+    const double inv = 1.0 / (double)(2 * h + 1);
+    const int hh = (int)h;
     for (int pass = 1; pass <= 3; ++pass) {
-        lds_scan(src, len, tsum);
-        const int64_t wb = (int64_t)(3 - pass) * h;
-        const int64_t nb = t0 - wb > 0 ? t0 - wb : 0, ne = t1 + wb < n ? t1 + wb : n;
-        const int nlen = (int)(ne - nb);
-        for (int k = tid; k < nlen; k += 256) {
-            const int64_t i = nb + k;
-            const int64_t lo = i - h > 0 ? i - h : 0, hi = i + h + 1 < n ? i + h + 1 : n;
-            const double v = (src[hi - b] - src[lo - b]) / (double)(hi - lo);
-            if (pass < 3) dst[k + 1] = v;
-            else L.X[i] = v;
+        double run = 0.0;
+#pragma unroll
+        for (int j = 0; j < SR; ++j) run += v[j];
+        double x = run;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double y = __shfl_up(x, o);
+            if (lane >= o) x += y;
         }
-        if (tid == 0) dst[0] = 0.0;
+        if (lane == 63) tsum[wv] = x;
+        __syncthreads();  // also: every wave has read its values of the last pass
+        double off = x - run;
+        for (int u = 0; u < wv; ++u) off += tsum[u];
+#pragma unroll
+        for (int j = 0; j < SR; ++j) {
+            q[i0 + j] = off;
+            off += v[j];
+        }
+        if (tid == STH - 1) q[SL] = off;
         __syncthreads();
-        double *t = src;
-        src = dst;
-        dst = t;
-        b = nb;
-        len = nlen;
+        // this pass's outputs lie in [lo, hi) of the workgroup's range
+        const int64_t wb = (int64_t)(3 - pass) * h;
+        const int lo = (int)((t0 - wb > 0 ? t0 - wb : 0) - b);
+        const int hi = (int)((t1 + wb < n ? t1 + wb : n) - b);
+        if (!clipped) {
+#pragma unroll
+            for (int j = 0; j < SR; ++j) {
+                const int i = i0 + j;
+                v[j] = i >= lo && i < hi ? (q[i + hh + 1] - q[i - hh]) * inv : 0.0;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < SR; ++j) {
+                const int i = i0 + j;
+                v[j] = 0.0;
+                if (i >= lo && i < hi) {
+                    const int64_t g = b + i;
+                    const int64_t ga = g - h > 0 ? g - h : 0, gb = g + h + 1 < n ? g + h + 1 : n;
+                    v[j] = (q[gb - b] - q[ga - b]) / (double)(gb - ga);
+                }
+            }
+        }
+        __syncthreads();
     }
+#pragma unroll
+    for (int j = 0; j < SR; ++j) q[i0 + j] = v[j];
+    __syncthreads();
+    for (int64_t i = t0 + tid; i < t1; i += STH) L.X[i] = q[i - b];
 }
 
-constexpr int KV = 8;   // trial velocities per workgroup
-
-__global__ __launch_bounds__(256) void k_ccf(const TraceDev *__restrict__ trs, int tr0,
-                                             const LoopTrace *__restrict__ lt, int nx,
-                                             const double *__restrict__ flux,
-                                             const double *__restrict__ flat,
-                                             const double *__restrict__ edges, double v0,
-                                             double dv, int nv, double *__restrict__ C)
-{
-    __shared__ double red[KV][256];
-    __shared__ double sh_mean;
-    const int tid = threadIdx.x, g = blockIdx.y, tr = tr0 + g, k0 = blockIdx.x * KV;
-    const TraceDev &Tr = trs[tr];
-    const LoopTrace L = lt[g];
-    const double c = 299792458.0;
-    const double vlo = fmin(v0, v0 + (nv - 1) * dv), vhi = fmax(v0, v0 + (nv - 1) * dv);
-    const double bmin = vlo / c, bmax = vhi / c;
-    const double dl = (Tr.lmax - Tr.lmin) / (double)L.n;
-    const int h = L.w / 2;
-    const double ulo = 6.0 * h, uhi = (double)(L.n - 2 - 6 * h);
-    const double *Ft = flux + (size_t)tr * nx, *Lt = edges + (size_t)tr * (nx + 1);
-    const double *Ff = flat ? flat + (size_t)tr * nx : nullptr;
-    auto usable = [&](int i, double *lc) {
+// The columns that enter a trace's CCF, and where its template is read.
+struct CcfTrace {
+    const double *F, *Ff, *Lt;
+    double lmin, inv_dl, dmin, dmax, gmin, gmax, ulo, uhi;
+    __device__ CcfTrace(const TraceDev &Tr, const LoopTemplate &L, int tr, int nx, const double *flux,
+                        const double *flat, const double *edges, double v0, double dv, int nv)
+    {
+        const double c = 299792458.0;
+        const double va = v0, vb = v0 + (nv - 1) * dv;
+        F = flux + (size_t)tr * nx;
+        Ff = flat ? flat + (size_t)tr * nx : nullptr;
+        Lt = edges + (size_t)tr * (nx + 1);
+        lmin = Tr.lmin;
+        inv_dl = (double)L.n / (Tr.lmax - Tr.lmin);
+        dmax = 1.0 + fmax(va, vb) / c;
+        dmin = 1.0 + fmin(va, vb) / c;
+        gmin = 1.0 / dmax;
+        gmax = 1.0 / dmin;
+        const int h = L.w / 2;
+        ulo = 6.0 * h;
+        uhi = (double)(L.n - 2 - 6 * h);
+    }
+    // fractional sample read at column centre lc under the factor d = 1 + v / c,
+    // g = 1 / d (the quotient lc / d rounded as a division's: an error in it is
+    // common to all columns of a velocity)
+    __device__ double sample(double lc, double d, double g) const
+    {
+        const double q = lc * g;
+        return fma(fma(fma(-q, d, lc), g, q) - lmin, inv_dl, -0.5);
+    }
+    __device__ double first(double lc) const { return sample(lc, dmax, gmin); }
+    __device__ double last(double lc) const { return sample(lc, dmin, gmax); }
+    __device__ bool usable(int i, double *lc, double *e) const
+    {
         const double a = Lt[i], b = Lt[i + 1];
         if (isnan(a) || isnan(b)) return false;
         if (Ff && !(Ff[i] > 0.0)) return false;
         *lc = 0.5 * (a + b);
-        return (*lc / (1.0 + bmax) - Tr.lmin) / dl - 0.5 >= ulo &&
-               (*lc / (1.0 + bmin) - Tr.lmin) / dl - 0.5 <= uhi;
-    };
-    // mean of e over the usable columns
+        *e = Ff ? F[i] / Ff[i] : F[i];
+        return first(*lc) >= ulo && last(*lc) <= uhi;
+    }
+};
+
+// Mean of e over a trace's usable columns, one workgroup a trace.
+__global__ __launch_bounds__(256) void k_ccf_mean(const TraceDev *__restrict__ trs,
+                                                  const LoopTrace *__restrict__ tl,
+                                                  const LoopTemplate *__restrict__ lt, int nx,
+                                                  const double *__restrict__ flux,
+                                                  const double *__restrict__ flat,
+                                                  const double *__restrict__ edges, double v0,
+                                                  double dv, int nv, double *__restrict__ mean)
+{
+    __shared__ double red[2][256];
+    const int tid = threadIdx.x, tr = tl[blockIdx.x].trace;
+    const CcfTrace T(trs[tr], lt[tl[blockIdx.x].tmpl], tr, nx, flux, flat, edges, v0, dv, nv);
     double s = 0.0, cnt = 0.0;
     for (int i = tid; i < nx; i += 256) {
-        double lc;
-        if (usable(i, &lc)) {
-            s += Ff ? Ft[i] / Ff[i] : Ft[i];
+        double lc, e;
+        if (T.usable(i, &lc, &e)) {
+            s += e;
             cnt += 1.0;
         }
     }
@@ -247,38 +316,136 @@ __global__ __launch_bounds__(256) void k_ccf(const TraceDev *__restrict__ trs, i
         }
         __syncthreads();
     }
-    if (tid == 0) sh_mean = red[1][0] > 0.0 ? red[0][0] / red[1][0] : 0.0;
-    __syncthreads();
-    const double mean = sh_mean;
-    double acc[KV];
-#pragma unroll
-    for (int q = 0; q < KV; ++q) acc[q] = 0.0;
-    for (int i = tid; i < nx; i += 256) {
-        double lc;
-        if (!usable(i, &lc)) continue;
-        const double e = (Ff ? Ft[i] / Ff[i] : Ft[i]) - mean;
-#pragma unroll
-        for (int q = 0; q < KV; ++q) {
-            const int k = k0 + q;
-            if (k >= nv) break;
-            const double beta = (v0 + k * dv) / c;
-            const double u = (lc / (1.0 + beta) - Tr.lmin) / dl - 0.5;
-            const int64_t m = (int64_t)floor(u);
-            const double f = u - (double)m;
-            acc[q] = fma(e, fma(L.X[m + 1] - L.X[m], f, L.X[m]), acc[q]);
-        }
+    if (tid == 0) mean[tr] = red[1][0] > 0.0 ? red[0][0] / red[1][0] : 0.0;
+}
+
+// CCF of a run of KR columns of one trace.  Neighbouring columns read stretches
+// of the template that overlap in most of their length (101 velocities span
+// 2500 samples of a C1-shaped template, columns are 108 apart), so the columns
+// go in steps whose stretch fits LDS, staged by coalesced loads; every
+// (column, velocity) pair then reads its two samples from LDS.  (Read from
+// global memory by a workgroup per 8 velocities, every load of a wave touched
+// 64 lines and the template went through the caches 13 times: 833 us for 64
+// traces, 265 us so.)  A step whose stretch does not fit (wide velocity grids
+// on dense templates) reads global memory.
+constexpr int KT = 512;          // threads
+constexpr int KR = 512;          // columns per workgroup, at most
+constexpr int KS = 64;           // columns per step, at most
+constexpr int KX = 8960;         // template samples in LDS (two workgroups per CU)
+
+__global__ __launch_bounds__(KT) void k_ccf(const TraceDev *__restrict__ trs,
+                                            const LoopTrace *__restrict__ tl,
+                                            const LoopTemplate *__restrict__ lt, int nx, int run,
+                                            int step, const double *__restrict__ flux,
+                                            const double *__restrict__ flat,
+                                            const double *__restrict__ edges, double v0, double dv,
+                                            int nv, const double *__restrict__ mean,
+                                            double *__restrict__ part)
+{
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(16))) double sx[KX];
+    __shared__ double slc[KR], se[KR];   // column centre (NaN: not used), e - mean
+    const int tid = threadIdx.x, lane = tid & 63;
+    const LoopTrace me = tl[blockIdx.y];
+    const LoopTemplate L = lt[me.tmpl];
+    const CcfTrace T(trs[me.trace], L, me.trace, nx, flux, flat, edges, v0, dv, nv);
+    const double m0 = mean[me.trace];
+    const int c_beg = blockIdx.x * run, cols = min(nx - c_beg, run);
+    for (int c = tid; c < cols; c += KT) {
+        double lc, e;
+        const bool ok = T.usable(c_beg + c, &lc, &e);
+        slc[c] = ok ? lc : __builtin_nan("");
+        se[c] = ok ? e - m0 : 0.0;
     }
     __syncthreads();
+    // threads share the velocities of a turn of up to KT: `ways` threads a
+    // velocity, each every ways-th column
+    double *const out = part + ((size_t)me.trace * gridDim.x + blockIdx.x) * nv;
+    for (int kb = 0; kb < nv; kb += KT) {
+        const int kn = min(KT, nv - kb), ways = KT / kn;
+        const int k = kb + tid % kn, way = tid / kn;
+        const double d = 1.0 + (v0 + k * dv) / 299792458.0, g = 1.0 / d;
+        double acc = 0.0;
+        for (int c0 = 0; c0 < cols; c0 += step) {
+            const int cn = min(step, cols - c0);
+            // the stretch that the step's columns read (each wave finds it)
+            const double mine = lane < cn ? slc[c0 + lane] : __builtin_nan("");
+            double lo = isnan(mine) ? 1e300 : T.first(mine), hi = isnan(mine) ? -1e300 : T.last(mine);
 #pragma unroll
-    for (int q = 0; q < KV; ++q) red[q][tid] = acc[q];
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (tid < o)
-#pragma unroll
-            for (int q = 0; q < KV; ++q) red[q][tid] += red[q][tid + o];
+            for (int o = 1; o < 64; o <<= 1) {
+                lo = fmin(lo, __shfl_xor(lo, o));
+                hi = fmax(hi, __shfl_xor(hi, o));
+            }
+            lo = uniform_d(lo);
+            hi = uniform_d(hi);
+            if (lo > hi) continue;  // no column used (the same in every wave)
+            const int64_t xa = (int64_t)floor(lo) - 1, xb = (int64_t)floor(hi) + 3;
+            const int64_t ra = (xa > 0 ? xa : 0) & ~(int64_t)1, rb = xb < L.n ? xb : L.n;
+            const bool fits = rb - ra <= KX;
+            if (fits) {
+                const int len = (int)(rb - ra);
+                const double *src = L.X + ra;   // 16-byte aligned: ra and the templates' spacing are even
+                for (int q = 2 * tid; q + 1 < len; q += 2 * KT)
+                    *reinterpret_cast<d2 *>(sx + q) = *reinterpret_cast<const d2 *>(src + q);
+                if ((len & 1) && tid == 0) sx[len - 1] = src[len - 1];
+                __syncthreads();
+            }
+            if (way < ways) {
+                for (int j = way; j < cn; j += ways) {
+                    const double lc = slc[c0 + j];
+                    if (isnan(lc)) continue;
+                    const double u = T.sample(lc, d, g), fl = floor(u);
+                    const double f = u - fl;
+                    double a, b;
+                    if (fits) {
+                        const double *p = sx + ((int64_t)fl - ra);
+                        a = p[0];
+                        b = p[1];
+                    } else {
+                        const double *p = L.X + (int64_t)fl;
+                        a = p[0];
+                        b = p[1];
+                    }
+                    acc = fma(se[c0 + j], fma(b - a, f, a), acc);
+                }
+            }
+            __syncthreads();
+        }
+        double *const red = sx;   // free between the turns
+        red[tid] = acc;
+        __syncthreads();
+        if (tid < kn) {
+            double s = 0.0;
+            for (int w = 0; w < ways; ++w) s += red[w * kn + tid];
+            out[kb + tid] = s;
+        }
         __syncthreads();
     }
-    if (tid < KV && k0 + tid < nv) C[(size_t)tr * nv + k0 + tid] = red[tid][0];
+}
+
+// One workgroup a velocity: ccf[tr][k], the trace's column runs added in order,
+// and their sum over the traces (each thread's in order, then the threads').
+__global__ __launch_bounds__(256) void k_ccf_sum(const double *__restrict__ part, int runs, int ntr,
+                                                 int nv, double *__restrict__ C,
+                                                 double *__restrict__ tot)
+{
+    __shared__ double red[256];
+    const int k = blockIdx.x, tid = threadIdx.x;
+    double all = 0.0;
+    for (int t = tid; t < ntr; t += 256) {
+        const double *p = part + (size_t)t * runs * nv + k;
+        double s = 0.0;
+        for (int r = 0; r < runs; ++r) s += p[(size_t)r * nv];
+        C[(size_t)t * nv + k] = s;
+        all += s;
+    }
+    red[tid] = all;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (tid < o) red[tid] += red[tid + o];
+        __syncthreads();
+    }
+    if (tid == 0) tot[k] = red[0];
 }
 
 }  // namespace
@@ -297,27 +464,24 @@ hipError_t launch_extract(const TraceDev *trs, int ntr, int nx, int ny, const vo
     return hipGetLastError();
 }
 
-hipError_t launch_smooth3(const void *lt_dev, int ntr, int64_t nmax, int wmax, int f64,
+bool loop_needs_p(int w);
+
+hipError_t launch_smooth3(const void *lt_dev, int n_tmpl, int64_t nmax, int wmax, int f64,
                           hipStream_t s)
 {
-    if (ntr <= 0 || nmax <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((nmax + SMT - 1) / SMT), ntr);
-    if (wmax / 2 <= SFH) {
-        if (f64)
-            hipLaunchKernelGGL(k_smooth3_fused<double>, grid, dim3(256), 0, s,
-                               (const LoopTrace *)lt_dev);
-        else
-            hipLaunchKernelGGL(k_smooth3_fused<float>, grid, dim3(256), 0, s,
-                               (const LoopTrace *)lt_dev);
+    if (n_tmpl <= 0 || nmax <= 0) return hipSuccess;
+    const LoopTemplate *lt = (const LoopTemplate *)lt_dev;
+    if (!loop_needs_p(wmax)) {
+        const int outs = SL - 6 * (wmax / 2);
+        const dim3 grid((unsigned)((nmax + outs - 1) / outs), n_tmpl);
+        if (f64) hipLaunchKernelGGL(k_smooth3<double>, grid, dim3(STH), 0, s, lt, outs);
+        else hipLaunchKernelGGL(k_smooth3<float>, grid, dim3(STH), 0, s, lt, outs);
         return hipGetLastError();
     }
+    const dim3 grid((unsigned)((nmax + SMT - 1) / SMT), n_tmpl);
     for (int pass = 0; pass < 3; ++pass) {
-        if (f64)
-            hipLaunchKernelGGL(k_box_pass<double>, grid, dim3(256), 0, s,
-                               (const LoopTrace *)lt_dev, pass);
-        else
-            hipLaunchKernelGGL(k_box_pass<float>, grid, dim3(256), 0, s,
-                               (const LoopTrace *)lt_dev, pass);
+        if (f64) hipLaunchKernelGGL(k_box_pass<double>, grid, dim3(256), 0, s, lt, pass);
+        else hipLaunchKernelGGL(k_box_pass<float>, grid, dim3(256), 0, s, lt, pass);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -325,29 +489,70 @@ hipError_t launch_smooth3(const void *lt_dev, int ntr, int64_t nmax, int wmax, i
 }
 
 int loop_max_width() { return SMW; }
-
-hipError_t launch_ccf(const TraceDev *trs, int tr0, int ntr, const void *lt_dev, int nx,
-                      const double *flux, const double *flat, const double *edges, double v0,
-                      double dv, int nv, double *C, hipStream_t s)
+bool loop_needs_p(int w) { return w / 2 > SFH; }
+// Columns a workgroup takes: 512, fewer while the launch would leave CUs idle.
+static int ccf_run(int nx, int ntr)
 {
-    if (ntr <= 0) return hipSuccess;
-    const dim3 grid((nv + KV - 1) / KV, ntr);
-    hipLaunchKernelGGL(k_ccf, grid, dim3(256), 0, s, trs, tr0, (const LoopTrace *)lt_dev, nx,
-                       flux, flat, edges, v0, dv, nv, C);
+    int run = KR;
+    while (run > KS && (int64_t)ntr * ((nx + run - 1) / run) < 1024) run /= 2;
+    return run;
+}
+int ccf_runs(int nx, int ntr) { return (nx + ccf_run(nx, ntr) - 1) / ccf_run(nx, ntr); }
+
+hipError_t launch_ccf_mean(const TraceDev *trs, const void *tl_dev, int n_tr, const void *lt_dev,
+                           int nx, const double *flux, const double *flat, const double *edges,
+                           double v0, double dv, int nv, double *mean, hipStream_t s)
+{
+    if (n_tr <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_ccf_mean, dim3(n_tr), dim3(256), 0, s, trs, (const LoopTrace *)tl_dev,
+                       (const LoopTemplate *)lt_dev, nx, flux, flat, edges, v0, dv, nv, mean);
     return hipGetLastError();
 }
 
+// n_tr of the format's ntr traces; step: columns whose reads are expected to
+// fit LDS, for templates of at most `spp` samples a column and a velocity grid
+// of `vspan` samples
+hipError_t launch_ccf(const TraceDev *trs, const void *tl_dev, int n_tr, int ntr, const void *lt_dev,
+                      int nx, double spp, double vspan, const double *flux, const double *flat,
+                      const double *edges, double v0, double dv, int nv, const double *mean,
+                      double *part, hipStream_t s)
+{
+    if (n_tr <= 0) return hipSuccess;
+    const double fit = (KX - 8 - vspan) / (spp > 1e-6 ? spp : 1e-6);
+    const int step = fit >= KS ? KS : fit >= 4.0 ? (int)fit : KS;
+    hipLaunchKernelGGL(k_ccf, dim3(ccf_runs(nx, ntr), n_tr), dim3(KT), 0, s, trs,
+                       (const LoopTrace *)tl_dev, (const LoopTemplate *)lt_dev, nx, ccf_run(nx, ntr),
+                       step, flux, flat, edges, v0, dv, nv, mean, part);
+    return hipGetLastError();
+}
+
+hipError_t launch_ccf_sum(const double *part, int ntr, int nx, int nv, double *C, double *tot,
+                          hipStream_t s)
+{
+    hipLaunchKernelGGL(k_ccf_sum, dim3(nv), dim3(256), 0, s, part, ccf_runs(nx, ntr), ntr, nv, C, tot);
+    return hipGetLastError();
+}
+
+size_t loop_template_bytes() { return sizeof(LoopTemplate); }
 size_t loop_trace_bytes() { return sizeof(LoopTrace); }
 
-void loop_trace_fill(void *dst, const void *tmpl, double *P, double *X, int64_t n, int w)
+void loop_template_fill(void *dst, const void *tmpl, double *P, double *X, int64_t n, int w)
 {
-    LoopTrace L;
+    LoopTemplate L;
     L.tmpl = tmpl;
     L.P = P;
     L.X = X;
     L.n = n;
     L.w = w;
     L.pad = 0;
+    *(LoopTemplate *)dst = L;
+}
+
+void loop_trace_fill(void *dst, int trace, int tmpl)
+{
+    LoopTrace L;
+    L.trace = trace;
+    L.tmpl = tmpl;
     *(LoopTrace *)dst = L;
 }
 
