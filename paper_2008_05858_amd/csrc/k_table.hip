@@ -491,11 +491,23 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                     sh_qmax[cpar] = -0x7fffffff;
                     sh_dmax[cpar] = 0u;
                 }
-                // the column's first spectrum values, loaded before the barrier
-                // so that their latency overlaps it
+                // The summed walk reads the spectrum in blocks of 64 bytes a column,
+                // four lanes a column (a lane reading its own column 16 bytes at
+                // a time fetched every line from L2 up to eight times: the lines
+                // of a CU's 768 columns do not fit its L1).  The first block of
+                // the wave's columns, loaded before the barrier so that its
+                // latency overlaps it; kst of the wave's own columns is there.
                 constexpr int G = SpecVec<ST>::G;
-                ST v0[G];
-                SpecVec<ST>::load(spec, ks_own, nspec, v0);
+                constexpr int BS = 64 / (int)sizeof(ST);   // samples of a block
+                const int scol = lane >> 2, schunk = lane & 3;
+                ST blk[4][G];
+                int kcol[4];
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    kcol[r] = kst[64 * wv + 16 * r + scol] + G * schunk;
+                    SpecVec<ST>::load(spec, kcol[r], nspec, blk[r]);
+                }
                 __syncthreads();
 
                 // ---- 2. this column's samples, in order.  Within one row run the
@@ -505,8 +517,68 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                 // run keeps the 9 moments sum phi rx^a ry^b (FP64) and turns
                 // them into deposits when the row changes.  Deposits go to the
                 // column's 4-row window wr[layer][x-slot][row] (rows rb..rb+3).
-                const int ks = kst[tid];
-                int ke = kst[tid + 1];
+                int ks = kst[tid], ke = kst[tid + 1];
+                // A segment that spans several node cells is walked once per
+                // cell, each column over its samples in that cell: x grows with
+                // the sample, so they are a range, whose ends are bisected on the
+                // exact cell (the same test for every cell, so each sample falls
+                // in one); y is monotone over a column unless its chord is
+                // flatter than its bend, then the samples are tested one by one.
+                bool ytest = false;
+                if (multi) {
+                    auto x_cell = [&](int k) {
+                        return ext_cell(horner<DX>(cxr, fma((double)k, dt, t0)), gsx, gxn);
+                    };
+                    auto y_cell = [&](int k) {
+                        return ext_cell(horner<DY>(cyr, fma((double)k, dt, t0)), gsy, gyn);
+                    };
+                    // first sample of [lo, hi) where the test holds (hi: none)
+                    auto first = [&](int lo, int hi, auto test) {
+                        while (lo < hi) {
+                            const int mid = lo + ((hi - lo) >> 1);
+                            if (test(mid)) hi = mid; else lo = mid + 1;
+                        }
+                        return lo;
+                    };
+                    if (ks < ke) {
+                        const int ca = x_cell(ks), cb = x_cell(ke - 1);
+                        if (ca > cxc || cb < cxc) {
+                            ke = ks;
+                        } else if (ca != cb) {
+                            const int kx = first(ks, ke, [&](int k) { return x_cell(k) >= cxc; });
+                            ke = first(kx, ke, [&](int k) { return x_cell(k) > cxc; });
+                            ks = kx;
+                        }
+                    }
+                    if (ks < ke && sg.cy0 != sg.cy1) {
+                        const double dk = (double)(ke - 1 - ks) * dt, bow = Tp->y2max * dk * dk;
+                        const double ya = horner<DY>(cyr, fma((double)ks, dt, t0));
+                        const double yb = horner<DY>(cyr, fma((double)(ke - 1), dt, t0));
+                        const double yl = fmin(ya, yb) - bow - 1e-9, yh = fmax(ya, yb) + bow + 1e-9;
+                        const int cl = ext_cell(yl, gsy, gyn), ch = ext_cell(yh, gsy, gyn);
+                        if (cl > cyc || ch < cyc) {
+                            ke = ks;
+                        } else if (cl != ch) {
+                            if (fabs(yb - ya) > bow && yb > ya) {
+                                const int ky = first(ks, ke, [&](int k) { return y_cell(k) >= cyc; });
+                                ke = first(ky, ke, [&](int k) { return y_cell(k) > cyc; });
+                                ks = ky;
+                            } else if (fabs(yb - ya) > bow) {
+                                const int ky = first(ks, ke, [&](int k) { return y_cell(k) <= cyc; });
+                                ke = first(ky, ke, [&](int k) { return y_cell(k) < cyc; });
+                                ks = ky;
+                            } else {
+                                ytest = true;
+                            }
+                        }
+                    }
+                    // the columns' ranges moved: their first blocks again
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        kcol[r] = __shfl(ks, 16 * r + scol) + G * schunk;
+                        SpecVec<ST>::load(spec, kcol[r], nspec, blk[r]);
+                    }
+                }
                 int nbx, nby;
                 double ax0, ax1, ay0, ay1;
                 cell_line(cxc, gsx, gxn, &nbx, &ax0, &ax1);
@@ -514,6 +586,154 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                 // fx = ax0 + ax1 * x with x = (q + rx - UC) / OS
                 const double fxa = fma(ax1, ((double)q - UC) / OS, ax0), fxb = ax1 / OS;
                 const double fyb = ay1 / OS;
+                // The summed walk (columns within one node cell, nearly all of
+                // them): within a column the phases are cubics in the sample's
+                // distance i from the column's last sample,
+                //   rx = e0 + e1 i + e2 i^2 + e3 i^3,  ry = f0 + f1 i + ...,
+                // so the moments follow from the column's power sums
+                // P_n = sum phi i^n, n <= 5, and a sample costs six additions,
+                //   S_0 += phi, S_n += S_(n-1)  (S_n = sum phi C(i + n, n)),
+                // instead of its position and nine moments.  Terms of the
+                // moments beyond i^5 only touch the field gradient's square
+                // (below 1e-8 of a deposit); what the cubics leave of the
+                // polynomials is below 1e-9 slot by the test in `summable`.
+                // A column whose row changes is summed in two runs, split at
+                // the sample jx (the sums before it are kept in SA).
+                double e0, e1, e2, e3, f0, f1, f2, f3;
+                int J = 0;
+                int row_s = 0, row_e = 0, jx = 0x7fffffff;
+                // the cubics about the column's last sample; far: what the
+                // polynomials hold beyond them at the column's other end
+                auto expand = [&](int klast, double *far) {
+                    const double ts = fma((double)klast, dt, t0);
+                    double bx[DX + 1], by[DY + 1];
+#pragma unroll
+                    for (int i = 0; i <= DX; ++i) bx[i] = cxr[i];
+#pragma unroll
+                    for (int i = 0; i <= DY; ++i) by[i] = cyr[i];
+#pragma unroll
+                    for (int i = 0; i < (far ? DX : 4); ++i)
+#pragma unroll
+                        for (int k = DX - 1; k >= i; --k) bx[k] = fma(ts, bx[k + 1], bx[k]);
+#pragma unroll
+                    for (int i = 0; i < (DY < 4 || far ? DY : 4); ++i)
+#pragma unroll
+                        for (int k = DY - 1; k >= i; --k) by[k] = fma(ts, by[k + 1], by[k]);
+                    const double h1 = -(double)OS * dt, h2 = -h1 * dt, h3 = -h2 * dt;
+                    e0 = fma(bx[0], (double)OS, UC - (double)q);
+                    e1 = bx[1] * h1;
+                    e2 = bx[2] * h2;
+                    e3 = bx[3] * h3;
+                    const double vy = fma(by[0], (double)OS, UC);
+                    f1 = by[1] * h1;
+                    f2 = by[2] * h2;
+                    f3 = by[3] * h3;
+                    row_e = (int)floor(vy);
+                    f0 = vy - floor(vy);
+                    if (far) {
+                        const double Jd = (double)J;
+                        double r = 0.0, hk = (double)OS * (Jd * Jd * Jd);
+#pragma unroll
+                        for (int k = 1; k <= 3; ++k) hk *= fabs(dt);
+#pragma unroll
+                        for (int k = 4; k <= (DX > DY ? DX : DY); ++k) {
+                            hk *= fabs(dt) * Jd;
+                            if (k <= DX) r = fma(fabs(bx[k]), hk, r);
+                            if (k <= DY) r = fma(fabs(by[k]), hk, r);
+                        }
+                        *far = r;
+                    }
+                };
+                auto summable = [&]() -> bool {
+                    J = ke - ks;
+                    double far = 0.0;
+                    expand(ke - 1, &far);
+                    // how far x and y leave their chords
+                    const double Jd = (double)J, J2 = Jd * Jd, J3 = J2 * Jd;
+                    const double bend = fma(fabs(e3), J3, fabs(e2) * J2);
+                    const double dev = fma(fabs(f3), J3, fabs(f2) * J2);
+                    // row phase of the first sample, counted from row_e
+                    const double is = Jd - 1.0;
+                    const double rs = fma(is, fma(is, fma(is, f3, f2), f1), f0);
+                    const double fs = floor(rs);
+                    row_s = row_e + (int)fs;
+                    bool ok = far <= 1e-9 && bend <= 0.05 && dev <= 0.05;
+                    if (row_s != row_e) {
+                        // the run's last sample in row_s: from the chord, then exact
+                        const double edge = fs < 0.0 ? 0.0 : 1.0;  // the row edge crossed
+                        auto ph = [&](double i) { return fma(i, fma(i, fma(i, f3, f2), f1), f0); };
+                        auto first_run = [&](double i) {  // sample i lies in row_s
+                            const double r = ph(i);
+                            return edge == 0.0 ? r < 0.0 : r >= 1.0;
+                        };
+                        double i = ceil((edge - f0) * __builtin_amdgcn_rcp(f1));
+                        i = fmin(fmax(i, 1.0), is);
+                        for (int it = 0; it < 4 && i < is && !first_run(i); ++it) i += 1.0;
+                        for (int it = 0; it < 4 && i > 1.0 && first_run(i - 1.0); ++it) i -= 1.0;
+                        ok = ok && fabs(fs) == 1.0 && first_run(i) && !first_run(i - 1.0);
+                        jx = J - (int)i;  // samples before jx are in row_s
+                        // one crossing only: y monotone over the column
+                        ok = ok && fabs(f1) * Jd > 2.0 * dev;
+                    } else {
+                        // no excursion between the ends (J samples, chord + dev)
+                        ok = ok && fmin(f0, rs) >= dev && fmax(f0, rs) <= 1.0 - dev;
+                    }
+                    return ok || J <= 0;
+                };
+                // a column that the sums do not describe goes sample by sample, each
+                // a run of its own (rare: its row phase within `dev` of an edge)
+                const bool single = !summable() || ytest;
+                double S[6], SA[6];
+                {
+                    const int Jmax = wave_reduce(single ? 0 : J, 0, [](int a, int b) { return max(a, b); });
+#pragma unroll
+                    for (int n = 0; n < 6; ++n) S[n] = SA[n] = 0.0;
+                    auto add = [&](double sv) {
+                        S[0] += sv;
+#pragma unroll
+                        for (int n = 1; n < 6; ++n) S[n] += S[n - 1];
+                    };
+                    auto add_split = [&](double sv, int j) {
+                        if (j == jx) {
+#pragma unroll
+                            for (int n = 0; n < 6; ++n) SA[n] = S[n];
+                        }
+                        add(sv);
+                    };
+                    // the blocks go through LDS (this wave's part of the band
+                    // buffer, 16-byte chunks permuted so that neither side meets
+                    // a bank twice), the next one's loads issued before this
+                    // one's samples
+                    unsigned char *const stg = bandbuf + wv * (64 * XS * 4);
+                    unsigned char *const put = stg + scol * 64 + ((schunk ^ (scol >> 2)) & 3) * 16;
+                    const unsigned char *const get = stg + lane * 64;
+                    const int sw = (lane >> 2) & 3;
+                    for (int j0 = 0; j0 < Jmax; j0 += BS) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            __builtin_memcpy(__builtin_assume_aligned(put + r * 16 * 64, 16), blk[r], 16);
+                        __builtin_amdgcn_wave_barrier();
+                        if (j0 + BS < Jmax)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                SpecVec<ST>::load(spec, kcol[r] + j0 + BS, nspec, blk[r]);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            ST v[G];
+                            __builtin_memcpy(v, __builtin_assume_aligned(get + ((c ^ sw) * 16), 16), 16);
+                            const int j = j0 + c * G;
+                            if (j + G <= J && !((unsigned)(jx - j) < (unsigned)G)) {
+#pragma unroll
+                                for (int e = 0; e < G; ++e) add((double)v[e]);
+                            } else if (j < J) {
+#pragma unroll
+                                for (int e = 0; e < G; ++e)
+                                    if (j + e < J) add_split((double)v[e], j + e);
+                            }
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
                 float wr[4][2][4];
 #pragma unroll
                 for (int l = 0; l < 4; ++l)
@@ -522,10 +742,6 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
 #pragma unroll
                         for (int r = 0; r < 4; ++r) wr[l][lr][r] = 0.0f;
                 double m[3][3];
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-#pragma unroll
-                    for (int b = 0; b < 3; ++b) m[a][b] = 0.0;
                 int runQy = kNone, rb = kNone;
                 bool run_in = false;
                 int qmin = 0x7fffffff, qmax = -0x7fffffff;
@@ -604,138 +820,110 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                             }
                     }
                 };
-                // Positions of the column's samples ks + j by forward differences
-                // of the FP64 format polynomials (exact up to rounding): px is
-                // u - q = OS x + UC - q (the slot phase rx), py is OS y + UC - runQy
-                // (the row phase ry of the current run).
-                double px[DX + 1], py[DY + 1];
-                auto setup = [&]() {
-                    const double ts = fma((double)ks, dt, t0);
-                    // Taylor coefficients at ts (synthetic division), in powers of
-                    // j dt, scaled to slots
-                    double bx[DX + 1], by[DY + 1];
-#pragma unroll
-                    for (int i = 0; i <= DX; ++i) bx[i] = cxr[i];
-#pragma unroll
-                    for (int i = 0; i <= DY; ++i) by[i] = cyr[i];
-#pragma unroll
-                    for (int i = 0; i < DX; ++i)
-#pragma unroll
-                        for (int k = DX - 1; k >= i; --k) bx[k] = fma(ts, bx[k + 1], bx[k]);
-#pragma unroll
-                    for (int i = 0; i < DY; ++i)
-#pragma unroll
-                        for (int k = DY - 1; k >= i; --k) by[k] = fma(ts, by[k + 1], by[k]);
-                    double h = (double)OS;
-#pragma unroll
-                    for (int i = 0; i <= (DX > DY ? DX : DY); ++i) {
-                        if (i <= DX) bx[i] *= h;
-                        if (i <= DY) by[i] *= h;
-                        h *= dt;
-                    }
-                    // forward differences at j = 0: d^k P = sum_i p_i k! S(i, k)
-#pragma unroll
-                    for (int k = 1; k <= DX; ++k) {
-                        double d = 0.0;
-#pragma unroll
-                        for (int i = DX; i >= k; --i) d = fma(bx[i], kFwd[i][k], d);
-                        px[k] = d;
-                    }
-#pragma unroll
-                    for (int k = 1; k <= DY; ++k) {
-                        double d = 0.0;
-#pragma unroll
-                        for (int i = DY; i >= k; --i) d = fma(by[i], kFwd[i][k], d);
-                        py[k] = d;
-                    }
-                    px[0] = bx[0] + (UC - (double)q);
-                    const double vy = by[0] + UC, fl = floor(vy);
-                    runQy = (int)fl;
-                    rb = runQy - 1;
-                    py[0] = vy - fl;
+                // ---- the column's runs of equal deposit row: moments, then deposits
+                auto times = [](const double *A, int n, int len, double a0, double a1, double a2,
+                                double a3) {
+                    double r = a0 * A[n];
+                    if (n + 1 < len) r = fma(a1, A[n + 1], r);
+                    if (n + 2 < len) r = fma(a2, A[n + 2], r);
+                    if (n + 3 < len) r = fma(a3, A[n + 3], r);
+                    return r;
                 };
-                auto sample = [&](double sv, auto mc) {
-                    double rx = px[0];
-                    double ry = py[0];
-                    // the row changes (rare) unless 0 <= ry < 1: one unsigned
-                    // compare of the high word (negative values have the sign bit)
-                    if (__builtin_expect((unsigned)(__double_as_longlong(ry) >> 32) >= 0x3ff00000u, 0)) {
-                        flush();
+                // power sums from the binomial ones (rising factorials)
+                    auto powers = [](const double *B, double *P) {
+                        P[0] = B[0];
+                        P[1] = B[1] - P[0];
+                        P[2] = fma(2.0, B[2], -fma(3.0, P[1], 2.0 * P[0]));
+                        P[3] = fma(6.0, B[3], -fma(6.0, P[2], fma(11.0, P[1], 6.0 * P[0])));
+                        P[4] = fma(24.0, B[4], -fma(10.0, P[3], fma(35.0, P[2], fma(50.0, P[1], 24.0 * P[0]))));
+                        P[5] = fma(120.0, B[5], -fma(15.0, P[4], fma(85.0, P[3], fma(225.0, P[2],
+                                                        fma(274.0, P[1], 120.0 * P[0])))));
+                    };
+                const bool split = row_s != row_e;
+                const double dist = (double)(J - jx);  // samples of a second run
+                // power sums of the run at hand, and of the second one (the whole
+                // column's less the first run's, moved to the column's last sample:
+                // sum phi (i + dist)^n by Horner in dist)
+                double P[6], PB[6];
+                {
+                    double PA[6];
+                    powers(SA, PA);
+                    powers(S, PB);
 #pragma unroll
-                        for (int a = 0; a < 3; ++a)
+                    for (int n = 0; n < 6; ++n) P[n] = split ? PA[n] : PB[n];
+                    if (split) {
 #pragma unroll
-                            for (int b = 0; b < 3; ++b) m[a][b] = 0.0;
-                        const double f = floor(ry);
-                        runQy += (int)f;
-                        ry -= f;
-                        py[0] = ry;
-                        run_in = false;
+                        for (int top = 5; top >= 1; --top)
+#pragma unroll
+                            for (int n = 5; n >= 6 - top; --n) PA[n] = fma(dist, PA[n - 1], PA[n]);
+#pragma unroll
+                        for (int n = 0; n < 6; ++n) PB[n] -= PA[n];
                     }
-                    bool in = true;
-                    if constexpr (decltype(mc)::value) {
-                        const double x = (rx + ((double)q - UC)) / OS;
-                        const double y = (ry + ((double)runQy - UC)) / OS;
-                        in = (ext_cell(x, gsx, gxn) == cxc) & (ext_cell(y, gsy, gyn) == cyc);
-                    }
-                    const double phi = in ? sv : 0.0;
-                    run_in |= in;
-                    const double e1 = phi * ry, e2 = e1 * ry, rx2 = rx * rx;
-                    m[0][0] += phi;
-                    m[0][1] += e1;
-                    m[0][2] += e2;
-                    m[1][0] = fma(phi, rx, m[1][0]);
-                    m[1][1] = fma(e1, rx, m[1][1]);
-                    m[1][2] = fma(e2, rx, m[1][2]);
-                    m[2][0] = fma(phi, rx2, m[2][0]);
-                    m[2][1] = fma(e1, rx2, m[2][1]);
-                    m[2][2] = fma(e2, rx2, m[2][2]);
-                    // next sample
-#pragma unroll
-                    for (int k = 0; k < DX; ++k) px[k] += px[k + 1];
-#pragma unroll
-                    for (int k = 0; k < DY; ++k) py[k] += py[k + 1];
-                };
-                // a trace segment that stays in one node cell (the usual case)
-                // needs no per-sample cell test: two instances of the loop
-                auto walk = [&](auto mc) {
-                    if (ks >= ke) return;
-                    setup();
-                    // spectrum values G at a time (one 16-byte load per lane),
-                    // the next group's load issued before this group's samples
-                    ST v[G], nv[G];
-#pragma unroll
-                    for (int e = 0; e < G; ++e) v[e] = v0[e];
-                    int kb = ks;
-                    for (; kb + G <= ke; kb += G) {  // whole groups: no per-sample test
-                        SpecVec<ST>::load(spec, min(kb + G, ke - 1), nspec, nv);
-#pragma unroll
-                        for (int e = 0; e < G; ++e) sample((double)v[e], mc);
-#pragma unroll
-                        for (int e = 0; e < G; ++e) v[e] = nv[e];
-                    }
-#pragma unroll
-                    for (int e = 0; e < G - 1; ++e)
-                        if (kb + e < ke) sample((double)v[e], mc);
-                    flush();
-                };
-                // A segment that spans several node cells is walked once per
-                // cell.  A column whose x range lies wholly outside this cell
-                // (with a margin far above rounding) has no sample in it and is
-                // skipped; one wholly inside it, on a segment within one y cell,
-                // needs no per-sample test.  Only the columns at a cell boundary
-                // take the tested walk, and a wave takes it only if one of its
-                // columns needs it.
-                bool tested = multi;
-                if (multi) {
-                    const double xl = ((double)q - UC) / OS - 1e-6;
-                    const double xh = ((double)q + 1.0 - UC) / OS + 1e-6;
-                    const int ca = ext_cell(xl, gsx, gxn), cb = ext_cell(xh, gsx, gxn);
-                    if (ca > cxc || cb < cxc) ke = ks;
-                    const bool inside = ca == cxc && cb == cxc && sg.cy0 == sg.cy1;
-                    tested = !__all(inside || ke <= ks);
                 }
-                if (tested) walk(std::true_type());
-                else walk(std::false_type());
+                const int nrun = J <= 0 ? 0 : single ? J : split ? 2 : 1;
+                for (int run = 0; __any(run < nrun); ++run) {
+                    if (run < nrun) {
+                        const bool first = split && run == 0 && !single;
+                        bool inside = true;
+                        int klast = ke - 1;
+                        if (single) {
+                            klast = ks + run;
+                            inside = !ytest || ext_cell(horner<DY>(cyr, fma((double)klast, dt, t0)), gsy,
+                                                        gyn) == cyc;
+                            P[0] = inside ? (double)spec[klast] : 0.0;
+#pragma unroll
+                            for (int n = 1; n < 6; ++n) P[n] = 0.0;
+                        } else if (run == 1) {
+#pragma unroll
+                            for (int n = 0; n < 6; ++n) P[n] = PB[n];
+                        }
+                        // (worked out again where it is used, not held or spilled
+                        // across the samples and the deposits)
+                        asm volatile("" : "+v"(klast));
+                        expand(klast, nullptr);
+                        // the cubics about the run's own last sample
+                        const double D = first ? dist : 0.0;
+                        const double c0 = fma(D, fma(D, fma(D, e3, e2), e1), e0);
+                        const double c1 = fma(D, fma(3.0 * D, e3, 2.0 * e2), e1), c2 = fma(3.0 * D, e3, e2);
+                        const double d0 = fma(D, fma(D, fma(D, f3, f2), f1), f0) +
+                                          (first ? (double)(row_e - row_s) : 0.0);
+                        const double d1 = fma(D, fma(3.0 * D, f3, 2.0 * f2), f1), d2 = fma(3.0 * D, f3, f2);
+                        // moments sum phi rx^a ry^b: the sequences sum phi w i^n
+                        // times the cubics, one factor after the other
+                        auto times = [](const double *A, int n, int len, double a0, double a1,
+                                        double a2, double a3) {
+                            double r = a0 * A[n];
+                            if (n + 1 < len) r = fma(a1, A[n + 1], r);
+                            if (n + 2 < len) r = fma(a2, A[n + 2], r);
+                            if (n + 3 < len) r = fma(a3, A[n + 3], r);
+                            return r;
+                        };
+                        double Xs[5], XX[4], Y[4], Z[4];
+#pragma unroll
+                        for (int n = 0; n < 5; ++n) Xs[n] = times(P, n, 6, c0, c1, c2, e3);
+#pragma unroll
+                        for (int n = 0; n < 4; ++n) Y[n] = times(P, n, 6, d0, d1, d2, f3);
+                        m[0][0] = P[0];
+                        m[0][1] = Y[0];
+                        m[0][2] = times(Y, 0, 4, d0, d1, d2, f3);
+                        m[1][0] = Xs[0];
+#pragma unroll
+                        for (int n = 0; n < 4; ++n) Z[n] = times(Xs, n, 5, d0, d1, d2, f3);
+                        m[1][1] = Z[0];
+                        m[1][2] = times(Z, 0, 4, d0, d1, d2, f3);
+#pragma unroll
+                        for (int n = 0; n < 4; ++n) XX[n] = times(Xs, n, 5, c0, c1, c2, e3);
+                        m[2][0] = XX[0];
+#pragma unroll
+                        for (int n = 0; n < 3; ++n) Z[n] = times(XX, n, 4, d0, d1, d2, f3);
+                        m[2][1] = Z[0];
+                        m[2][2] = times(Z, 0, 3, d0, d1, d2, f3);
+                        runQy = first ? row_s : row_e;
+                        if (run == 0) rb = first ? row_s - 1 : row_e - 1;
+                        run_in = inside;
+                        flush();
+                    }
+                }
                 // the left-slot halves belong to slot c - 1: hand them (and the
                 // window's first row) to the column on the left through LDS
                 float *xw = reinterpret_cast<float *>(bandbuf);
