@@ -116,14 +116,19 @@ inline int table_tw(int kw) { return (kTableThreads - kw) / kOS; }
 // Default run of a frame of `tiles` tiles.  A longer run shares each trace
 // segment's search, sums and stencil among more tiles, but leaves fewer
 // workgroups (768 fit the GPU, and several rounds of them are needed to even
-// out their uneven work).  Measured, run of 2 / 4 / 8 tiles: 512 x 452 (150
-// tiles) 0.13 / 0.19 / 0.23 ms; 2048^2 (2368) 0.20 / 0.26 / 0.36; 3000^2 (5076)
-// 0.28 / 0.33 / 0.39; 4096^2 (9472) 0.40 / 0.44 / 0.47 alone but 1.17 / 1.12 /
-// 1.15 as a batch of four and 2.10 / 1.97 / 1.91 of eight; 48-cell 6144^2
-// (22848) 10.6 / 9.7 / 10.4; 7500^2 (31490) 0.98 / 0.94 / 0.98; 9216^2 (47520)
-// 1.35 / 1.35 / 1.32.  It depends on the frame alone, so a frame has the same
-// bits alone and in a batch.
-inline int table_chunk(int tiles) { return tiles < 6144 ? 2 : tiles < 32768 ? 4 : kTableChunk; }
+// out their uneven work).  Measured in us, run of 2 / 3 / 4 / 8 tiles: 512 x 452
+// (150 tiles) 127 / 144 / 192 / 227; 2048^2 (2368) 174 / 176 / 221 / 291; 3000^2
+// (5076) 234 / 259 / 278 / 299; 3989 x 2929 (6624), two frames 208 / 189 / 204 /
+// 197; 4096^2 (9472) 340 / 334 / 361 / 381, four frames 1015 / 983 / 970 / 966;
+// 6144^2 (21120) 632 / 598 / 623 / 638, three frames 1583 / 1503 / 1481 / 1434;
+// 48-cell 6144^2 (22848) 5860 / 5530 / 5400 / 5460; 7500^2 (31490) 836 / 780 / 805
+// / 809; 9216^2 (47520) 1165 / 1112 / 1106 / 1083.  (Runs of one tile: 122 us at
+// 512 x 452, slower above: 182 at 2048^2.)  It depends on the frame alone, so a
+// frame has the same bits alone and in a batch.
+inline int table_chunk(int tiles)
+{
+    return tiles < 6144 ? 2 : tiles < 16384 ? 3 : tiles < 32768 ? 4 : kTableChunk;
+}
 // Work units of the table path: runs of `chunk` tiles down one column.
 inline int table_units(int ntx, int nty, int chunk) { return ntx * ((nty + chunk - 1) / chunk); }
 

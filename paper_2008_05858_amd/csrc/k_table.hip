@@ -18,9 +18,12 @@
 //   1. gives each thread one slot column and finds that column's samples
 //      (an interpolated guess, secant steps, an exact test on the FP64
 //      format polynomial);
-//   2. walks those samples in order (spectrum values read four at a time,
-//      FP64 positions, FP64 moment sums per row run) into the column's
-//      private 4-row deposit window held in registers;
+//   2. sums those samples (spectrum values through LDS in blocks of 64 bytes
+//      a column): within a column the position is a cubic in the sample
+//      number, so five FP64 power sums of the values give the FP64 moments of
+//      a run of equal deposit row, and these the 16 deposits, which go to the
+//      column's private 4-row window held in registers.  A column that the
+//      cubics do not describe goes sample by sample;
 //   3. for each band of 4 consecutive deposit rows, stores the deposits of
 //      every slot column in LDS as fp16 hi + lo parts (scaled by a power of
 //      two), and applies the stencils as one dense product per node layer:
@@ -32,8 +35,6 @@
 //      pre-split from the table built at load time.  The four layer
 //      partials are added in FP64, in a fixed order, into the FP64 LDS tile.
 // The summation order is fixed, so reruns are bitwise identical.
-#include <type_traits>
-
 #include "dev_common.h"
 
 namespace e2e {
@@ -43,20 +44,9 @@ namespace {
 constexpr int kNone = 0x3fffffff;  // "no row yet"; far from any real row
 constexpr int kUnf = 64;           // traces one tile can hand on to the next
 
-// k! S(i, k), S the Stirling numbers of the second kind: the k-th forward
-// difference at 0 of j^i (unit step), for i, k <= 7
-__device__ constexpr double kFwd[8][8] = {
-    {1, 0, 0, 0, 0, 0, 0, 0},
-    {0, 1, 0, 0, 0, 0, 0, 0},
-    {0, 1, 2, 0, 0, 0, 0, 0},
-    {0, 1, 6, 6, 0, 0, 0, 0},
-    {0, 1, 14, 36, 24, 0, 0, 0},
-    {0, 1, 30, 150, 240, 120, 0, 0},
-    {0, 1, 62, 540, 1560, 1800, 720, 0},
-    {0, 1, 126, 1806, 8400, 16800, 15120, 5040},
-};
-
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef float fl2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u4s __attribute__((ext_vector_type(4)));
 // four spectrum values (two for FP64), read at any 4-byte-aligned index
@@ -121,6 +111,14 @@ __device__ int wave_reduce(int v, int ident, Op op)
     v = op(v, __builtin_amdgcn_update_dpp(ident, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
     v = op(v, __builtin_amdgcn_update_dpp(ident, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
     return __builtin_amdgcn_readlane(v, 63);
+}
+
+// LDS written by some lanes of a wave and read by others of the same wave: the
+// hardware keeps their order, the compiler has to as well
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 template <int KW, int DX, int DY, typename ST>
@@ -440,8 +438,10 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                 const double ua = u_of(k0), um = u_of(km), ub = u_of(k1 - 1);
                 double d1 = 0.0, d2 = 0.0;
                 if (km > k0 && km < k1 - 1) {  // three distinct samples (u grows with k)
-                    d1 = (double)(km - k0) / (um - ua);
-                    d2 = ((double)(k1 - 1 - km) / (ub - um) - d1) / (ub - ua);
+                    // (a guess: the hardware reciprocal will do)
+                    d1 = (double)(km - k0) * __builtin_amdgcn_rcp(um - ua);
+                    d2 = fma((double)(k1 - 1 - km), __builtin_amdgcn_rcp(ub - um), -d1) *
+                         __builtin_amdgcn_rcp(ub - ua);
                 }
                 auto search = [&](int qq) -> int {
                     const double uq = (double)qq;
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                     sh_qmax[cpar] = -0x7fffffff;
                     sh_dmax[cpar] = 0u;
                 }
-                // The summed walk reads the spectrum in blocks of 64 bytes a column,
+                // The sums read the spectrum in blocks of 64 bytes a column,
                 // four lanes a column (a lane reading its own column 16 bytes at
                 // a time fetched every line from L2 up to eight times: the lines
                 // of a CU's 768 columns do not fit its L1).  The first block of
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                 const int scol = lane >> 2, schunk = lane & 3;
                 ST blk[4][G];
                 int kcol[4];
-                __builtin_amdgcn_wave_barrier();
+                wave_sync();
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     kcol[r] = kst[64 * wv + 16 * r + scol] + G * schunk;
@@ -510,13 +510,12 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                 }
                 __syncthreads();
 
-                // ---- 2. this column's samples, in order.  Within one row run the
-                // 16 deposits (2 x-slots x 2 rows x 4 nodes) are polynomials of
-                // degree <= 2 in the sub-slot phases (rx, ry), because the CIC
-                // weights and the node weights are both affine in them; so the
-                // run keeps the 9 moments sum phi rx^a ry^b (FP64) and turns
-                // them into deposits when the row changes.  Deposits go to the
-                // column's 4-row window wr[layer][x-slot][row] (rows rb..rb+3).
+                // ---- 2. this column's samples.  Within one row run the 16 deposits
+                // (2 x-slots x 2 rows x 4 nodes) are polynomials of degree <= 2 in
+                // the sub-slot phases (rx, ry), because the CIC weights and the
+                // node weights are both affine in them; so a run needs the 9
+                // moments sum phi rx^a ry^b (FP64).  Deposits go to the column's
+                // 4-row window wr[layer][x-slot][row] (rows rb..rb+3).
                 int ks = kst[tid], ke = kst[tid + 1];
                 // A segment that spans several node cells is walked once per
                 // cell, each column over its samples in that cell: x grows with
@@ -586,19 +585,21 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                 // fx = ax0 + ax1 * x with x = (q + rx - UC) / OS
                 const double fxa = fma(ax1, ((double)q - UC) / OS, ax0), fxb = ax1 / OS;
                 const double fyb = ay1 / OS;
-                // The summed walk (columns within one node cell, nearly all of
-                // them): within a column the phases are cubics in the sample's
-                // distance i from the column's last sample,
+                // Within a column the phases are cubics in the sample's distance i
+                // from the column's last sample,
                 //   rx = e0 + e1 i + e2 i^2 + e3 i^3,  ry = f0 + f1 i + ...,
                 // so the moments follow from the column's power sums
-                // P_n = sum phi i^n, n <= 5, and a sample costs six additions,
+                // P_n = sum phi i^n, n <= 4, and a sample costs five additions,
                 //   S_0 += phi, S_n += S_(n-1)  (S_n = sum phi C(i + n, n)),
-                // instead of its position and nine moments.  Terms of the
-                // moments beyond i^5 only touch the field gradient's square
-                // (below 1e-8 of a deposit); what the cubics leave of the
-                // polynomials is below 1e-9 slot by the test in `summable`.
-                // A column whose row changes is summed in two runs, split at
-                // the sample jx (the sums before it are kept in SA).
+                // instead of its position and nine moments.  What the cubics
+                // leave of the polynomials is below 1e-9 slot by the test in
+                // `summable`.  A column whose row changes is summed in two runs,
+                // split at the sample jx (the sums before it are kept in SA).
+                // Against a walk that gave each sample its position and moments:
+                // a 48-cell 6144^2 frame (86 samples a column) 9.6 ms -> 5.4, a
+                // 32-cell 9216^2 frame (11 a column) 1.265 -> 1.05, four of them
+                // 3.83 -> 3.39.  VALU issue bounds it (80% of the cycles): the
+                // 32-cell frames' in the runs' moments and deposits and the bands.
                 double e0, e1, e2, e3, f0, f1, f2, f3;
                 int J = 0;
                 int row_s = 0, row_e = 0, jx = 0x7fffffff;
@@ -657,7 +658,13 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                     const double rs = fma(is, fma(is, fma(is, f3, f2), f1), f0);
                     const double fs = floor(rs);
                     row_s = row_e + (int)fs;
-                    bool ok = far <= 1e-9 && bend <= 0.05 && dev <= 0.05;
+                    // what the moments leave out below, of a deposit (gx, gy: the
+                    // field's gradients a slot)
+                    const double gx = fabs(fxb), gy = fabs(fyb), g = fmax(gx, gy);
+                    const double cub = fma(fabs(e3), J3, fabs(f3) * J3);
+                    const double left = fma(cub, bend + dev + g,
+                                            fma(g, fma(bend, bend, dev * dev), gx * gy * dev));
+                    bool ok = far <= 1e-9 && left <= 1e-7 && bend <= 0.05 && dev <= 0.05;
                     if (row_s != row_e) {
                         // the run's last sample in row_s: from the chord, then exact
                         const double edge = fs < 0.0 ? 0.0 : 1.0;  // the row edge crossed
@@ -680,23 +687,25 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                     }
                     return ok || J <= 0;
                 };
-                // a column that the sums do not describe goes sample by sample, each
-                // a run of its own (rare: its row phase within `dev` of an edge)
+                // A column that the sums do not describe goes sample by sample, each
+                // a run of its own (rare: a row phase within `dev` of an edge, y
+                // turning at a grid line, a window of about 100 pixels with a fine
+                // grid or a strong bend).
                 const bool single = !summable() || ytest;
-                double S[6], SA[6];
+                double S[5], SA[5];
                 {
                     const int Jmax = wave_reduce(single ? 0 : J, 0, [](int a, int b) { return max(a, b); });
 #pragma unroll
-                    for (int n = 0; n < 6; ++n) S[n] = SA[n] = 0.0;
+                    for (int n = 0; n < 5; ++n) S[n] = SA[n] = 0.0;
                     auto add = [&](double sv) {
                         S[0] += sv;
 #pragma unroll
-                        for (int n = 1; n < 6; ++n) S[n] += S[n - 1];
+                        for (int n = 1; n < 5; ++n) S[n] += S[n - 1];
                     };
                     auto add_split = [&](double sv, int j) {
                         if (j == jx) {
 #pragma unroll
-                            for (int n = 0; n < 6; ++n) SA[n] = S[n];
+                            for (int n = 0; n < 5; ++n) SA[n] = S[n];
                         }
                         add(sv);
                     };
@@ -712,7 +721,7 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
                             __builtin_memcpy(__builtin_assume_aligned(put + r * 16 * 64, 16), blk[r], 16);
-                        __builtin_amdgcn_wave_barrier();
+                        wave_sync();
                         if (j0 + BS < Jmax)
 #pragma unroll
                             for (int r = 0; r < 4; ++r)
@@ -731,7 +740,7 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                                     if (j + e < J) add_split((double)v[e], j + e);
                             }
                         }
-                        __builtin_amdgcn_wave_barrier();
+                        wave_sync();
                     }
                 }
                 float wr[4][2][4];
@@ -820,45 +829,37 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                             }
                     }
                 };
-                // ---- the column's runs of equal deposit row: moments, then deposits
-                auto times = [](const double *A, int n, int len, double a0, double a1, double a2,
-                                double a3) {
-                    double r = a0 * A[n];
-                    if (n + 1 < len) r = fma(a1, A[n + 1], r);
-                    if (n + 2 < len) r = fma(a2, A[n + 2], r);
-                    if (n + 3 < len) r = fma(a3, A[n + 3], r);
-                    return r;
+                // ---- the column's runs of equal deposit row: moments, then deposits.
+                // Power sums from the binomial ones (rising factorials).
+                auto powers = [](const double *B, double *P) {
+                    P[0] = B[0];
+                    P[1] = B[1] - P[0];
+                    P[2] = fma(2.0, B[2], -fma(3.0, P[1], 2.0 * P[0]));
+                    P[3] = fma(6.0, B[3], -fma(6.0, P[2], fma(11.0, P[1], 6.0 * P[0])));
+                    P[4] = fma(24.0, B[4],
+                               -fma(10.0, P[3], fma(35.0, P[2], fma(50.0, P[1], 24.0 * P[0]))));
                 };
-                // power sums from the binomial ones (rising factorials)
-                    auto powers = [](const double *B, double *P) {
-                        P[0] = B[0];
-                        P[1] = B[1] - P[0];
-                        P[2] = fma(2.0, B[2], -fma(3.0, P[1], 2.0 * P[0]));
-                        P[3] = fma(6.0, B[3], -fma(6.0, P[2], fma(11.0, P[1], 6.0 * P[0])));
-                        P[4] = fma(24.0, B[4], -fma(10.0, P[3], fma(35.0, P[2], fma(50.0, P[1], 24.0 * P[0]))));
-                        P[5] = fma(120.0, B[5], -fma(15.0, P[4], fma(85.0, P[3], fma(225.0, P[2],
-                                                        fma(274.0, P[1], 120.0 * P[0])))));
-                    };
                 const bool split = row_s != row_e;
                 const double dist = (double)(J - jx);  // samples of a second run
                 // power sums of the run at hand, and of the second one (the whole
                 // column's less the first run's, moved to the column's last sample:
                 // sum phi (i + dist)^n by Horner in dist)
-                double P[6], PB[6];
-                {
-                    double PA[6];
+                double P[5], PB[5];
+                powers(S, P);
+                if (__any(split && !single)) {
+                    double PA[5];
                     powers(SA, PA);
-                    powers(S, PB);
 #pragma unroll
-                    for (int n = 0; n < 6; ++n) P[n] = split ? PA[n] : PB[n];
-                    if (split) {
-#pragma unroll
-                        for (int top = 5; top >= 1; --top)
-#pragma unroll
-                            for (int n = 5; n >= 6 - top; --n) PA[n] = fma(dist, PA[n - 1], PA[n]);
-#pragma unroll
-                        for (int n = 0; n < 6; ++n) PB[n] -= PA[n];
+                    for (int n = 0; n < 5; ++n) {
+                        PB[n] = P[n];
+                        P[n] = split ? PA[n] : P[n];
                     }
+#pragma unroll
+                    for (int top = 4; top >= 1; --top)
+#pragma unroll
+                        for (int n = 4; n >= 5 - top; --n) PA[n] = fma(dist, PA[n - 1], PA[n]);
+#pragma unroll
+                    for (int n = 0; n < 5; ++n) PB[n] -= PA[n];
                 }
                 const int nrun = J <= 0 ? 0 : single ? J : split ? 2 : 1;
                 for (int run = 0; __any(run < nrun); ++run) {
@@ -872,10 +873,10 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                                                         gyn) == cyc;
                             P[0] = inside ? (double)spec[klast] : 0.0;
 #pragma unroll
-                            for (int n = 1; n < 6; ++n) P[n] = 0.0;
+                            for (int n = 1; n < 5; ++n) P[n] = 0.0;
                         } else if (run == 1) {
 #pragma unroll
-                            for (int n = 0; n < 6; ++n) P[n] = PB[n];
+                            for (int n = 0; n < 5; ++n) P[n] = PB[n];
                         }
                         // (worked out again where it is used, not held or spilled
                         // across the samples and the deposits)
@@ -888,36 +889,34 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                         const double d0 = fma(D, fma(D, fma(D, f3, f2), f1), f0) +
                                           (first ? (double)(row_e - row_s) : 0.0);
                         const double d1 = fma(D, fma(3.0 * D, f3, 2.0 * f2), f1), d2 = fma(3.0 * D, f3, f2);
-                        // moments sum phi rx^a ry^b: the sequences sum phi w i^n
-                        // times the cubics, one factor after the other
-                        auto times = [](const double *A, int n, int len, double a0, double a1,
-                                        double a2, double a3) {
-                            double r = a0 * A[n];
-                            if (n + 1 < len) r = fma(a1, A[n + 1], r);
-                            if (n + 2 < len) r = fma(a2, A[n + 2], r);
-                            if (n + 3 < len) r = fma(a3, A[n + 3], r);
-                            return r;
-                        };
-                        double Xs[5], XX[4], Y[4], Z[4];
-#pragma unroll
-                        for (int n = 0; n < 5; ++n) Xs[n] = times(P, n, 6, c0, c1, c2, e3);
-#pragma unroll
-                        for (int n = 0; n < 4; ++n) Y[n] = times(P, n, 6, d0, d1, d2, f3);
+                        // moments sum phi rx^a ry^b, from the sequences
+                        // sum phi w i^n one factor after the other.  The deposits
+                        // take the product rx ry as it is, the second powers times
+                        // the field's gradient, so the latter are cut at second
+                        // order (a column's quadratic part is 1e-4 slot at most in
+                        // ordinary formats, its cubic part 1e-7, the gradient
+                        // 1e-2 a slot: 3e-9 of a deposit; tested in `summable`)
+                        const double X0 = fma(e3, P[3], fma(c2, P[2], fma(c1, P[1], c0 * P[0])));
+                        const double X1 = fma(e3, P[4], fma(c2, P[3], fma(c1, P[2], c0 * P[1])));
+                        const double X2 = fma(c2, P[4], fma(c1, P[3], c0 * P[2]));
+                        const double X3 = fma(c1, P[4], c0 * P[3]);
+                        const double Y0 = fma(f3, P[3], fma(d2, P[2], fma(d1, P[1], d0 * P[0])));
+                        const double Y1 = fma(d2, P[3], fma(d1, P[2], d0 * P[1]));
+                        const double Y2 = fma(d1, P[3], d0 * P[2]);
+                        const double Z0 = fma(f3, X3, fma(d2, X2, fma(d1, X1, d0 * X0)));
+                        const double Z1 = fma(d2, X3, fma(d1, X2, d0 * X1)), Z2 = fma(d1, X3, d0 * X2);
+                        const double W0 = fma(e3, X3, fma(c2, X2, fma(c1, X1, c0 * X0)));
+                        const double W1 = fma(c2, X3, fma(c1, X2, c0 * X1)), W2 = fma(c1, X3, c0 * X2);
+                        const double V0 = fma(d2, W2, fma(d1, W1, d0 * W0)), V1 = fma(d1, W2, d0 * W1);
                         m[0][0] = P[0];
-                        m[0][1] = Y[0];
-                        m[0][2] = times(Y, 0, 4, d0, d1, d2, f3);
-                        m[1][0] = Xs[0];
-#pragma unroll
-                        for (int n = 0; n < 4; ++n) Z[n] = times(Xs, n, 5, d0, d1, d2, f3);
-                        m[1][1] = Z[0];
-                        m[1][2] = times(Z, 0, 4, d0, d1, d2, f3);
-#pragma unroll
-                        for (int n = 0; n < 4; ++n) XX[n] = times(Xs, n, 5, c0, c1, c2, e3);
-                        m[2][0] = XX[0];
-#pragma unroll
-                        for (int n = 0; n < 3; ++n) Z[n] = times(XX, n, 4, d0, d1, d2, f3);
-                        m[2][1] = Z[0];
-                        m[2][2] = times(Z, 0, 3, d0, d1, d2, f3);
+                        m[0][1] = Y0;
+                        m[0][2] = fma(d2, Y2, fma(d1, Y1, d0 * Y0));
+                        m[1][0] = X0;
+                        m[1][1] = Z0;
+                        m[1][2] = fma(d2, Z2, fma(d1, Z1, d0 * Z0));
+                        m[2][0] = W0;
+                        m[2][1] = V0;
+                        m[2][2] = fma(d1, V1, d0 * V0);
                         runQy = first ? row_s : row_e;
                         if (run == 0) rb = first ? row_s - 1 : row_e - 1;
                         run_in = inside;
@@ -991,7 +990,7 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
                             nl[r] = tid + 1 < NCOL ? xw[(tid + 1) * XS + l * 4 + r] : 0.0f;
-                        unsigned hh[5], ll[5];
+                        float v[6];
 #pragma unroll
                         for (int u = 0; u < 5; ++u) {
                             float a = 0.0f, b = 0.0f;
@@ -999,18 +998,25 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                             if (u >= 1) a = da == 1 ? wr[l][1][u - 1] : a;
                             if (u < 4) b = dn == 0 ? nl[u] : b;
                             if (u >= 1) b = dn == 1 ? nl[u - 1] : b;
-                            const float v = (a + b) * dsc;
-                            const _Float16 h = (_Float16)v;
-                            const _Float16 lo = (_Float16)(v - (float)h);
-                            hh[u] = __builtin_bit_cast(unsigned short, h);
-                            ll[u] = __builtin_bit_cast(unsigned short, lo);
+                            v[u + 1] = (a + b) * dsc;
                         }
-                        w0h[l] = hh[0] << 16;
-                        w0l[l] = ll[0] << 16;
-                        w1h[l] = (unsigned long long)(hh[1] | (hh[2] << 16)) |
-                                 ((unsigned long long)(hh[3] | (hh[4] << 16)) << 32);
-                        w1l[l] = (unsigned long long)(ll[1] | (ll[2] << 16)) |
-                                 ((unsigned long long)(ll[3] | (ll[4] << 16)) << 32);
+                        v[0] = 0.0f;
+                        // pairs (0, row 0), (row 1, row 2), (row 3, row 4): hi parts
+                        // rounded two at a time, the remainders exact by the
+                        // mixed-precision fma, then the lo parts
+                        unsigned hp[3], lp[3];
+#pragma unroll
+                        for (int u = 0; u < 3; ++u) {
+                            const fl2 w = {v[2 * u], v[2 * u + 1]};
+                            const h2 h = __builtin_convertvector(w, h2);
+                            const fl2 r = {fmaf(-(float)h.x, 1.0f, w.x), fmaf(-(float)h.y, 1.0f, w.y)};
+                            hp[u] = __builtin_bit_cast(unsigned, h);
+                            lp[u] = __builtin_bit_cast(unsigned, __builtin_convertvector(r, h2));
+                        }
+                        w0h[l] = hp[0];
+                        w0l[l] = lp[0];
+                        w1h[l] = (unsigned long long)hp[1] | ((unsigned long long)hp[2] << 32);
+                        w1l[l] = (unsigned long long)lp[1] | ((unsigned long long)lp[2] << 32);
                     }
                 }
                 __syncthreads();  // the exchange area becomes the band
