@@ -88,6 +88,7 @@ static void free_scratch(Scratch *s)
     hipFree(s->segs);
     hipFree(s->work);
     hipFree(s->specptrs);
+    hipFree(s->parts);
     hipFree(s->err);
     hipFree(s->counter);
     if (s->err_host) hipHostFree(s->err_host);
@@ -788,6 +789,21 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
             return st;
     }
 
+    // Few tiles of the per-sample FP64 kernels: each in units of its own, their
+    // sums in scratch (the same bits without, where the scratch does not fit)
+    size_t sep_items = 0;
+    if ((kind == E2E_PSF_GAUSS_ERF && prec != E2E_PREC_F32) ||
+        (kind == E2E_PSF_SEPARABLE && prec == E2E_PREC_F64))
+        for (int i = 0; i < n; ++i) sep_items += nodes[i] == 0 ? tiles[i] : 0;
+    const size_t part_bytes = sep_items * kSepUnits * 256 * sizeof(double);
+    if (!noalloc && sep_items > 0 && sep_items <= kSepSplitItems &&
+        ctx->used + temp_bytes + scratch_need + part_bytes + sep_items * sizeof(int) <= ctx->budget) {
+        if (grow(&sc->parts, &sc->parts_cap, part_bytes + sep_items * sizeof(int), "units") == E2E_OK)
+            cfg.parts = {reinterpret_cast<int *>((char *)sc->parts + part_bytes), (double *)sc->parts};
+        else
+            (void)hipGetLastError();  // no memory for them: without
+    }
+
     // spectra pointers (device), host spectra copied to temporaries
     sc->h_specptrs.assign(nslots_total, nullptr);
     for (int i = 0; i < n; ++i) {
@@ -1002,11 +1018,11 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         std::string parts;  // the render launches: node count and items of each
         for (auto &g : groups)
             parts += std::to_string(g.nodes) + ":" + std::to_string(g.w1 - g.w0) + ",";
-        char key[320];
-        snprintf(key, sizeof key, "%d/%d/%d/%d/%d/%d/%d/%d/%s/%d/%lld/%d/%p/%p", kind, cfg.kw,
+        char key[352];
+        snprintf(key, sizeof key, "%d/%d/%d/%d/%d/%d/%d/%d/%s/%d/%lld/%d/%p/%p/%p", kind, cfg.kw,
                  cfg.resident, cfg.degx, cfg.degy, cfg.spec_f64, prec, n, parts.c_str(), maxw,
                  any_noise ? (long long)maxpix : 0ll, (int)any_noise, (void *)sc->frames_dev,
-                 (void *)sc->work);
+                 (void *)sc->work, (void *)cfg.parts.part);
         auto it = sc->graphs.find(key);
         if (it == sc->graphs.end()) {
             GraphRec g;

@@ -58,6 +58,8 @@ struct Scratch {
     size_t work_cap = 0;
     const void **specptrs = nullptr;
     size_t specptrs_cap = 0;
+    void *parts = nullptr;       // SepParts: partial sums, then units
+    size_t parts_cap = 0;
     int *err = nullptr;
     int *counter = nullptr;
     int *err_host = nullptr;

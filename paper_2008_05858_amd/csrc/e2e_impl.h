@@ -132,6 +132,21 @@ inline int table_chunk(int tiles)
 // Work units of the table path: runs of `chunk` tiles down one column.
 inline int table_units(int ntx, int nty, int chunk) { return ntx * ((nty + chunk - 1) / chunk); }
 
+// Partial sums of a small frame's per-sample tiles (k_sep.hip): units of each
+// work item, and [item][kSepUnits][256 pixels] sums (null: no partial sums).
+constexpr int kSepUnits = 12;
+// Tiles of a launch up to which they are summed in units of their own.  Measured
+// without / with, us: 512 x 256 (512 tiles), one trace of 8 / 40 / 110 samples a
+// pixel 30 / 32, 58 / 34, 110 / 42, eight traces of 110 222 / 93; 1024 x 512 (2048),
+// eight traces of 100 253 / 139; 1024^2 (4096), four traces of 40 81 / 73, eight
+// 121 / 94; eight 512 x 256 frames (4096) 149 / 128; 2048 x 1024 (8192), four traces
+// of 20 85 / 102, eight of 100 448 / 257 (but 200 MB of sums).
+constexpr size_t kSepSplitItems = 4096;
+struct SepParts {
+    int *units = nullptr;
+    double *part = nullptr;
+};
+
 // Compile-time choices of a render launch (shared by every frame of it).
 struct KernelCfg {
     int kw;             // table cells per kernel side (table path)
@@ -141,6 +156,7 @@ struct KernelCfg {
     int precision;      // E2E_PREC_*
     int nodes;          // separable: nodes a pixel column; SFI: 1 = product of terms;
                         // 0 = the per-sample kernels
+    SepParts parts;     // per-sample FP64 kernels of small frames
     int resident;       // persistent launches: workgroups per CU (0 = path default)
 };
 
