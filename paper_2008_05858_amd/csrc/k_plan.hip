@@ -40,10 +40,9 @@ __device__ int first_at_or_above(const double *cx, double t0, double dt, double 
     return lo;
 }
 
-__global__ void k_plan(const FrameDev *__restrict__ frames, int *__restrict__ err)
+// (tile column, trace) idx of frame F, whose spectrum pointers are spec
+__device__ __forceinline__ void plan_one(const FrameDev &F, const void *const *spec, int idx)
 {
-    const FrameDev &F = frames[blockIdx.y];
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= F.ntx * F.ntr) return;
     int c = idx / F.ntr, tr = idx % F.ntr;
     const TraceDev &T = F.tr[tr];
@@ -64,7 +63,7 @@ __global__ void k_plan(const FrameDev *__restrict__ frames, int *__restrict__ er
         tfd.t0 = t0;
         tfd.dt = dt;
         tfd.scale = T.thr * F.flux_scale;
-        tfd.spec = F.spec[T.slot];
+        tfd.spec = spec[T.slot];
         F.tf[tr] = tfd;
     }
     int X0 = c * F.tw, X1 = min(X0 + F.tw, F.nx);
@@ -140,26 +139,38 @@ __global__ void k_plan(const FrameDev *__restrict__ frames, int *__restrict__ er
     F.segs[(size_t)c * F.ntr + tr] = S;
 }
 
+__global__ void k_plan(const FrameDev *__restrict__ frames, int *__restrict__ err)
+{
+    const FrameDev &F = frames[blockIdx.y];
+    plan_one(F, F.spec, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// The same for one frame whose record and spectrum pointers come in the
+// argument; the first block also stores them for the render kernels.
+__global__ void k_plan_put(FrameParams p, FrameDev *__restrict__ frame_dst,
+                           const void **__restrict__ spec_dst)
+{
+    const int t = threadIdx.x;
+    if (blockIdx.x == 0) {
+        if (t < p.nslots) spec_dst[t] = p.spec[t];
+        if (t == 0) *frame_dst = p.f;
+    }
+    plan_one(p.f, p.spec, blockIdx.x * blockDim.x + t);
+}
+
 __global__ void k_fill_i32(int *p, int n, int v)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
 }
 
-// Copies the frame record and spectrum pointers carried in the argument.
-__global__ void k_put_params(FrameParams p, FrameDev *frame_dst, const void **spec_dst)
-{
-    const int t = threadIdx.x;
-    if (t < p.nslots) spec_dst[t] = p.spec[t];
-    if (t == 0) *frame_dst = p.f;
-}
-
 }  // namespace
 
-hipError_t launch_put_params(const FrameParams &p, FrameDev *frame_dst, const void **spec_dst,
-                             hipStream_t s)
+hipError_t launch_plan_put(const FrameParams &p, FrameDev *frame_dst, const void **spec_dst,
+                           hipStream_t s)
 {
-    hipLaunchKernelGGL(k_put_params, dim3(1), dim3(kParamSlots), 0, s, p, frame_dst, spec_dst);
+    const int blocks = max((p.f.ntx * p.f.ntr + 255) / 256, 1);
+    hipLaunchKernelGGL(k_plan_put, dim3(blocks), dim3(256), 0, s, p, frame_dst, spec_dst);
     return hipGetLastError();
 }
 
