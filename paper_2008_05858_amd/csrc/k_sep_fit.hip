@@ -4,17 +4,18 @@
 // nodes, then the nodes are rendered.
 //
 // Within one pixel column of a trace (the samples with floor(x + 1/2) = i)
-// and one row anchor, a sample's footprint is a smooth function of its
-// offset s = x - i in [-1/2, 1/2): both windows stand still, and y, sigma_x
-// and sigma_y vary smoothly along the trace.  So the footprint is taken as
-// its Chebyshev interpolant on the M nodes s_m,
-//     w(s) = sum_m L_m(s) w(s_m),
+// and one row anchor, a sample's footprint is a smooth function of its place
+// tau in [-1, 1] between the column's first and last sample: both windows
+// stand still, and x, y, sigma_x and sigma_y vary smoothly along the trace.
+// So the footprint is taken as its Chebyshev interpolant on the M nodes tau_m,
+//     w(tau) = sum_m L_m(tau) w(tau_m),
 // and the column's samples add up to M node weights
-//     sum_k phi_k w(s_k) = sum_m Phi_m w(s_m),
-//     Phi_m = sum_k phi_k L_m(s_k) = 1/M (mu_0 + 2 sum_{p>=1} mu_p T_p(2 s_m)),
-//     mu_p = sum_k phi_k T_p(2 s_k),
+//     sum_k phi_k w(tau_k) = sum_m Phi_m w(tau_m),
+//     Phi_m = sum_k phi_k L_m(tau_k) = 1/M (mu_0 + 2 sum_{p>=1} mu_p T_p(tau_m)),
+//     mu_p = sum_k phi_k T_p(tau_k),
 // FP64 sums over the samples by the recurrence of phi T_p.  For a Gaussian of
-// inverse width kappa along the trace the interpolation error is below
+// inverse width kappa along the trace (x is linear in tau within the bend that
+// sep_fit_nodes allows) the interpolation error is below
 // 2.2 (kappa / 4)^M / sqrt(M!) of the footprint's peak (Cramer's bound on the
 // Hermite functions): the host picks M = 10 or 12 so that this stays below
 // 4e-9 (sep_fit_nodes), a tenth of the FP32 rounding of the frame.  Columns
@@ -25,10 +26,13 @@
 // What bounds it: the C2-shaped frame (9216^2, 340 traces, 108 samples a
 // column) used to evaluate 36 normal CDFs for each of 3.4e8 samples in every
 // tile it reaches, VALU issue in all of the per-sample kernels.  Here a sample
-// costs ~30 FP64 instructions and a tenth as many nodes the pixel integrals:
-// 56.8 ms (FP64 VALU) and 35.0 ms (fp16 hi/lo MFMA) -> 5.4 ms at either
-// precision, still VALU issue (about 2e9 instructions, two thirds of the
-// issue slots) on the node's pixel integrals and the column sums.
+// costs ~14 FP64 instructions (two mirrored samples share a recurrence; no
+// position: nodes lie at sample numbers) and a tenth as many nodes the pixel
+// integrals: 56.8 ms (FP64 VALU) and 35.0 ms (fp16 hi/lo MFMA) -> 4.9 ms at
+// either precision, still VALU issue, on the node's pixel integrals, the
+// column sums and the FP64 additions of the products.  (With nodes at given x,
+// found by Newton steps, and a position and a full recurrence for each sample
+// it took 5.4 ms.)
 //
 // A workgroup owns a 64 x 32 tile, three of them fit a CU (LDS).  Per trace:
 // the first sample of each column (exact test on the FP64 format), the column
@@ -39,8 +43,8 @@
 // sigma; wave w multiplies column block w, F += Gy diag(Phi) Gx^T, by
 // v_mfma_f32_16x16x4_f32 over 16 nodes at a time, each FP32 partial then added
 // to FP64 sums.  One form serves all precisions: FP64 products
-// (v_mfma_f64_16x16x4_f64) took 6.8 ms, FP32 sums throughout 5.5 ms, fp16
-// hi/lo halves 6.4 ms (splitting the weights costs more than the matrix cores
+// (v_mfma_f64_16x16x4_f64) took 6.8 ms where this took 5.4, FP32 sums throughout
+// 5.5 ms, fp16 hi/lo halves 6.4 ms (splitting the weights costs more than the matrix cores
 // save), and this is also the closest to the exact frame of the last three.
 // Pixel integrals are taken in FP64: P(z) = 2a phi(z) sum_i A_i (z a)^(2i) /
 // (2i)!, a = h / 2 = 1 / (2 sigma), from exp(-z u) expanded under the integral
@@ -61,7 +65,7 @@ constexpr int TY = kMfmaTH;            // 32 rows = 2 blocks of 16
 constexpr int NCOL = TX + 2 * kMaxH;   // pixel columns whose samples reach the tile
 constexpr int NENT = 2 * NCOL;         // list entries: at most two row anchors a column
 
-// cos((2m + 1) pi / (2M)): the nodes are s_m = half of these
+// the nodes tau_m = cos((2m + 1) pi / (2M))
 __device__ constexpr double kNode10[10] = {
     0.98768834059513777, 0.8910065241883679, 0.70710678118654757, 0.4539904997395468,
     0.15643446504023092, -0.15643446504023092, -0.4539904997395468, -0.70710678118654757,
@@ -219,7 +223,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
     __shared__ unsigned short ent[NENT];
     __shared__ unsigned short tlist[kMaxTileTraces];
     __shared__ unsigned smask[4][2];
-    __shared__ double snode[M];             // 2 s_m
+    __shared__ double snode[M];             // tau_m
     __shared__ int sh_item, sh_nent, sh_raw;
     float *const ybuf = buf + TX * LS;       // the rows' lines follow the columns'
 
@@ -421,39 +425,74 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
 #pragma unroll
                     for (int p = 0; p < M; ++p) mu[p] = 0.0;
                     if (fit) {
-                        // groups of four samples go round the quad's lanes, so a
-                        // quad reads 64 consecutive bytes
+                        // Samples in pairs (ks + j, ke - 1 - j), whose tau are
+                        // opposite: T_p is even or odd, so a pair costs one
+                        // recurrence on its sum and one on its difference, in
+                        // steps of T_2.  Groups of four pairs go round the quad's
+                        // lanes, so a quad reads 64 consecutive bytes a side.
                         const int ks = kst[c], ke = kst[c + 1];
-                        int k = ks + 4 * part;
-                        const double xi = (double)(X0 - H + c);
+                        const int J = ke - ks, hJ = J >> 1;
+                        const double step = 2.0 * recip((double)(J - 1));
                         const bool test = (en & kEntTest) != 0;
                         const double ar = (double)((int)((en >> 7) & 63) - kMaxH + Y0);
-                        auto sample = [&](int kk, double phi) {
-                            const double t = fma((double)kk, dt, t0);
-                            const double y2 = 4.0 * (horner<DX>(cxr, t) - xi);
-                            if (test && floor(horner<DY>(cyr, t) + 0.5) != ar) phi = 0.0;
-                            double pa = phi, pb = 0.5 * y2 * phi;
-                            mu[0] += pa;
-                            mu[1] += pb;
+                        auto keep = [&](int k) {  // this sample has the entry's row anchor
+                            return !test || floor(horner<DY>(cyr, fma((double)k, dt, t0)) + 0.5) == ar;
+                        };
+                        auto pair = [&](int j, double pf, double pb) {
+                            if (test) {
+                                pf = keep(ks + j) ? pf : 0.0;
+                                pb = keep(ke - 1 - j) ? pb : 0.0;
+                            }
+                            const double tau = fma((double)j, step, -1.0);
+                            const double w2 = fma(tau + tau, tau, -1.0), w = w2 + w2;  // T_2, 2 T_2
+                            double ea = pf + pb, eb = w2 * ea;      // T_0, T_2
+                            const double d = pf - pb;
+                            double oa = tau * d, ob = fma(w, oa, -oa);  // T_1, T_3
+                            mu[0] += ea;
+                            mu[1] += oa;
+                            mu[2] += eb;
+                            mu[3] += ob;
 #pragma unroll
-                            for (int p = 2; p < M; ++p) {
-                                const double pc = fma(y2, pb, -pa);
-                                mu[p] += pc;
-                                pa = pb;
-                                pb = pc;
+                            for (int p = 4; p < M; p += 2) {
+                                const double ec = fma(w, eb, -ea), oc = fma(w, ob, -oa);
+                                mu[p] += ec;
+                                mu[p + 1] += oc;
+                                ea = eb;
+                                eb = ec;
+                                oa = ob;
+                                ob = oc;
                             }
                         };
-                        // the next four values are loaded while these are added
-                        ST v[4], nv[4];
-                        if (k + 4 <= ke) Vec4<ST>::load(spec, k, v);
-                        for (; k + 4 <= ke; k += 16) {
-                            Vec4<ST>::load(spec, k + 20 <= ke ? k + 16 : k, nv);
+                        // (where registers allow, the next four pairs are loaded
+                        // while these are added)
+                        constexpr bool kAhead = sizeof(ST) == 4 && DX <= 4;
+                        int j = 4 * part;
+                        ST vf[4], vb[4];
+                        auto fetch = [&](int jj, ST *f, ST *b) {
+                            Vec4<ST>::load(spec, ks + jj, f);
+                            Vec4<ST>::load(spec, ke - 4 - jj, b);
+                        };
+                        if (kAhead && j + 4 <= hJ) fetch(j, vf, vb);
+                        for (; j + 4 <= hJ; j += 16) {
+                            ST nf[4], nb[4];
+                            if constexpr (kAhead) fetch(j + 20 <= hJ ? j + 16 : j, nf, nb);
+                            else fetch(j, vf, vb);
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) sample(k + j, (double)v[j]);
+                            for (int e = 0; e < 4; ++e) pair(j + e, (double)vf[e], (double)vb[3 - e]);
+                            if constexpr (kAhead) {
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) v[j] = nv[j];
+                                for (int e = 0; e < 4; ++e) {
+                                    vf[e] = nf[e];
+                                    vb[e] = nb[e];
+                                }
+                            }
                         }
-                        for (; k < ke; ++k) sample(k, (double)spec[k]);
+                        for (; j < hJ; ++j) pair(j, (double)spec[ks + j], (double)spec[ke - 1 - j]);
+                        if ((J & 1) && part == 0 && keep(ks + hJ)) {  // the middle one: tau = 0
+                            const double phi = (double)spec[ks + hJ];
+#pragma unroll
+                            for (int p = 0; p < M; p += 2) mu[p] += p & 2 ? -phi : phi;
+                        }
                     }
 #pragma unroll
                     for (int p = 0; p < M; ++p) mu[p] = quad_sum(mu[p]);
@@ -515,18 +554,11 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                         ay = floor(y + 0.5);
                         if (xaxis) phi = (float)(spec_at(spec, k) * scale);
                     } else {
-                        // t with x(t) = x by a chord and two Newton steps
-                        // from the column's first sample
+                        const int ks = kst[c], ke = kst[c + 1];
+                        const double t = fma(0.5 * fma((double)(ke - 1 - ks), snode[m],
+                                                       (double)(ks + ke - 1)), dt, t0);
                         ax = (double)(X0 - H + c);
-                        x = fma(0.5, snode[m], ax);
-                        double t = fma((double)kst[c], dt, t0), dx;
-                        double xt = horner_d<DX>(cxr, t, &dx);
-                        double r = recip(dx);
-                        t = fma(x - xt, r, t);
-                        xt = horner_d<DX>(cxr, t, &dx);
-                        r = recip(dx);
-                        t = fma(x - xt, r, t);
-                        t = fma(x - horner<DX>(cxr, t), r, t);
+                        x = horner<DX>(cxr, t);
                         y = horner<DY>(cyr, t);
                         ay = (double)((int)((en >> 7) & 63) - kMaxH + Y0);
                         if (xaxis) phi = sphi[e][m];
