@@ -118,6 +118,7 @@ extern "C" void e2e_destroy(e2e_ctx *ctx)
         delete kv.second;
     }
     for (auto &kv : ctx->scratch) free_scratch(kv.second);
+    hipFree(ctx->loop_ws);
     for (auto &p : ctx->prof_pending) {
         hipEventDestroy(p.a);
         hipEventDestroy(p.b);

@@ -121,6 +121,8 @@ struct e2e_ctx {
     e2e::Server *srv = nullptr;  // owned by serve.cpp
     e2e::NoAlloc noalloc;        // the allocation-free render's device array
     std::map<std::string, e2e::TuneRec> tune;  // by workload shape (guarded by mu)
+    void *loop_ws = nullptr;      // a CCF's workspace, kept between calls (guarded by mu)
+    size_t loop_cap = 0;
     std::mutex srv_mu;
 };
 
