@@ -399,9 +399,10 @@ e2e_status e2e_extract(e2e_ctx *ctx, e2e_format_id fmt, const void *frame, int32
  * sum_tr ccf[tr][k] (k in 1 .. n_v - 2) and its two neighbours.
  * on_device: flux / flat / edges / templates / ccf_out are device pointers
  * (templates is still a host array of n_templates pointers).  ccf_out may
- * be NULL.  The library allocates up to 192 MB of smoothed templates at a
+ * be NULL.  The library needs up to 192 MB of smoothed templates at a
  * time (n FP64 values per template in use, 2 n for windows above 1025 samples;
- * at least one) and partial sums for the call.
+ * at least one) and partial sums; the context keeps a workspace of up to 256 MB
+ * between calls, larger ones are allocated for the call.
  * Errors: E2E_EINVAL (NULL pointers, n_v < 3, dv = 0, smooth_px <= 0, a
  * moving-mean width above 4095 samples, too few templates, bad dtype),
  * E2E_ENOTFOUND, E2E_ENOMEM, E2E_EDEVICE.
