@@ -53,3 +53,19 @@ def test_frames_against_the_oracle_and_a_large_batch(name, kind):
         outs = gpu_util.render_batch([sc] * count, [rq] * count, [ld] * count)
         assert all(np.array_equal(g, b) for b in outs)
     ld.free()
+
+
+def test_a_budget_without_room_for_the_units_gives_the_same_bits():
+    """15 tiles' partial sums take 15 x 12 x 2 KB, more than this context has."""
+    from tests import gpu_util
+    from paper_2008_05858_amd import e2e as E
+    sc, rq = _scene("erf", 61.0, traces=2), Request(rv_mps=12.0)
+    print("case budget", flush=True)
+    small = E.e2e_create(0, 200_000)
+    try:
+        ld = gpu_util.P.Loaded(small, sc)
+        a = gpu_util.render(sc, rq, loaded=ld, context=small)
+        ld.free()
+    finally:
+        E.e2e_destroy(small)
+    assert np.array_equal(a, gpu_util.render(sc, rq))
