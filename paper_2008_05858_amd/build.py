@@ -14,7 +14,7 @@ SOURCES = ["api.cpp", "serve.cpp", "k_plan.hip", "k_table.hip", "k_sep.hip",
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall",
          "-Wno-unused-function", "-Wno-unused-result", "-Wno-unused-value",
-         # packed FP32 arithmetic stays off on the test machines
+         # packed FP32 arithmetic stays off
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
