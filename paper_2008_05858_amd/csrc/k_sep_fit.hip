@@ -52,6 +52,7 @@
 // recurrence); the Gaussian runs along the window by two multiplications a
 // pixel.  Eight terms leave an absolute error below 4e-10 for sigma >= 0.58.
 // The order of every sum is fixed: the result is deterministic.
+#include "sample_index.h"
 #include "sep_stage.h"
 
 namespace e2e {
@@ -314,7 +315,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                     } else {
                         lo = k + 1;
                         for (int step = 1; lo < hi; step *= 2) {
-                            const int c = min(hi, lo + step - 1);
+                            const int c = hi - lo < step ? hi : lo + step - 1;
                             if (xp(c) < col) lo = c + 1;
                             else { hi = c; break; }
                         }
@@ -555,8 +556,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                         if (xaxis) phi = (float)(spec_at(spec, k) * scale);
                     } else {
                         const int ks = kst[c], ke = kst[c + 1];
-                        const double t = fma(0.5 * fma((double)(ke - 1 - ks), snode[m],
-                                                       (double)(ks + ke - 1)), dt, t0);
+                        const double t = fma(node_sample(ks, ke, snode[m]), dt, t0);
                         ax = (double)(X0 - H + c);
                         x = horner<DX>(cxr, t);
                         y = horner<DY>(cyr, t);
