@@ -36,6 +36,7 @@
 //      partials are added in FP64, in a fixed order, into the FP64 LDS tile.
 // The summation order is fixed, so reruns are bitwise identical.
 #include "dev_common.h"
+#include "sample_index.h"
 
 namespace e2e {
 
@@ -66,33 +67,35 @@ __device__ __forceinline__ void st4(double *p, d4 v)
     *reinterpret_cast<d2 *>(p + 2) = d2{v.z, v.w};
 }
 
+// G values from `off` past a place in the spectrum, 0 past its end.  end: the
+// spectrum's last G values; room: how far the place lies before them.
 template <typename ST>
 struct SpecVec;
 template <>
 struct SpecVec<float> {
     static constexpr int G = 4;
-    __device__ static void load(gptr<float> p, int k, int n, float v[4])
+    __device__ static void load(gptr<float> end, int room, int off, float v[4])
     {
-        if (__builtin_expect(k + 4 <= n, 1)) {
-            const f4u q = *(const __attribute__((address_space(1))) f4u *)(p + k);
+        if (__builtin_expect(group_inside(room, off), 1)) {
+            const f4u q = *(const __attribute__((address_space(1))) f4u *)(end + (off - room));
             v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = k + e < n ? p[k + e] : 0.0f;
+            for (int e = 0; e < 4; ++e) v[e] = value_inside(room, 4, off, e) ? end[off - room + e] : 0.0f;
         }
     }
 };
 template <>
 struct SpecVec<double> {
     static constexpr int G = 2;
-    __device__ static void load(gptr<double> p, int k, int n, double v[2])
+    __device__ static void load(gptr<double> end, int room, int off, double v[2])
     {
-        if (__builtin_expect(k + 2 <= n, 1)) {
-            const d2u q = *(const __attribute__((address_space(1))) d2u *)(p + k);
+        if (__builtin_expect(group_inside(room, off), 1)) {
+            const d2u q = *(const __attribute__((address_space(1))) d2u *)(end + (off - room));
             v[0] = q.x; v[1] = q.y;
         } else {
-            v[0] = k < n ? p[k] : 0.0;
-            v[1] = k + 1 < n ? p[k + 1] : 0.0;
+            v[0] = value_inside(room, 2, off, 0) ? end[off - room] : 0.0;
+            v[1] = 0.0;
         }
     }
 };
@@ -501,12 +504,13 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                 constexpr int BS = 64 / (int)sizeof(ST);   // samples of a block
                 const int scol = lane >> 2, schunk = lane & 3;
                 ST blk[4][G];
-                int kcol[4];
+                int room[4];   // of the lane's place in each column (group_room)
+                const gptr<ST> spec_end = spec + (nspec - G);
                 wave_sync();
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    kcol[r] = kst[64 * wv + 16 * r + scol] + G * schunk;
-                    SpecVec<ST>::load(spec, kcol[r], nspec, blk[r]);
+                    room[r] = group_room(nspec, G, kst[64 * wv + 16 * r + scol]) - G * schunk;
+                    SpecVec<ST>::load(spec_end, room[r], 0, blk[r]);
                 }
                 __syncthreads();
 
@@ -574,8 +578,8 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                     // the columns' ranges moved: their first blocks again
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        kcol[r] = __shfl(ks, 16 * r + scol) + G * schunk;
-                        SpecVec<ST>::load(spec, kcol[r], nspec, blk[r]);
+                        room[r] = group_room(nspec, G, __shfl(ks, 16 * r + scol)) - G * schunk;
+                        SpecVec<ST>::load(spec_end, room[r], 0, blk[r]);
                     }
                 }
                 int nbx, nby;
@@ -702,8 +706,8 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
 #pragma unroll
                         for (int n = 1; n < 5; ++n) S[n] += S[n - 1];
                     };
-                    auto add_split = [&](double sv, int j) {
-                        if (j == jx) {
+                    auto add_split = [&](double sv, unsigned j) {
+                        if (j == (unsigned)jx) {
 #pragma unroll
                             for (int n = 0; n < 5; ++n) SA[n] = S[n];
                         }
@@ -717,27 +721,28 @@ __global__ __launch_bounds__(kTableThreads, 3) void k_render_table(
                     unsigned char *const put = stg + scol * 64 + ((schunk ^ (scol >> 2)) & 3) * 16;
                     const unsigned char *const get = stg + lane * 64;
                     const int sw = (lane >> 2) & 3;
-                    for (int j0 = 0; j0 < Jmax; j0 += BS) {
+                    // (unsigned: a column can hold nearly 2^31 samples)
+                    for (unsigned j0 = 0; j0 < (unsigned)Jmax; j0 += BS) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
                             __builtin_memcpy(__builtin_assume_aligned(put + r * 16 * 64, 16), blk[r], 16);
                         wave_sync();
-                        if (j0 + BS < Jmax)
+                        if (j0 + BS < (unsigned)Jmax)
 #pragma unroll
                             for (int r = 0; r < 4; ++r)
-                                SpecVec<ST>::load(spec, kcol[r] + j0 + BS, nspec, blk[r]);
+                                SpecVec<ST>::load(spec_end, room[r], (int)(j0 + BS), blk[r]);
 #pragma unroll
                         for (int c = 0; c < 4; ++c) {
                             ST v[G];
                             __builtin_memcpy(v, __builtin_assume_aligned(get + ((c ^ sw) * 16), 16), 16);
-                            const int j = j0 + c * G;
-                            if (j + G <= J && !((unsigned)(jx - j) < (unsigned)G)) {
+                            const unsigned j = j0 + c * G;
+                            if (j + G <= (unsigned)J && !((unsigned)jx - j < (unsigned)G)) {
 #pragma unroll
                                 for (int e = 0; e < G; ++e) add((double)v[e]);
-                            } else if (j < J) {
+                            } else if (j < (unsigned)J) {
 #pragma unroll
                                 for (int e = 0; e < G; ++e)
-                                    if (j + e < J) add_split((double)v[e], j + e);
+                                    if (j + e < (unsigned)J) add_split((double)v[e], j + e);
                             }
                         }
                         wave_sync();
