@@ -599,31 +599,36 @@ e2e_status e2e::validate_req(e2e_ctx *ctx, const e2e_render_req *r, FormatRes **
 // column); the interpolation error 2.2 (kappa / 4)^M / sqrt(M!) of the peak
 // is kept below 4e-9, a tenth of the FP32 rounding of the frame: 10 nodes up
 // to kappa = 1.13 (sigma >= 0.9 px), 12 up to 1.72 (sigma >= 0.58 px, also
-// where the kernel's eight-term pixel integrals end).  The measured error of
-// the frames is no larger than the per-sample kernels' (5e-8 of the norm).
+// where the kernel's eight-term pixel integrals end).  Measured largest error /
+// error of the norm, on 2048^2 to 4096 x 2048 frames of sigma 0.8 .. 1.6 px:
+// 0.65e-7 to 1.0e-7 of the peak / 2.9e-8 to 3.1e-8 under E2E_PREC_F64, against
+// 0.9e-7 to 1.4e-7 / 3.7e-8 to 5.6e-8 per sample; 1.2e-7 to 1.7e-7 / 4.3e-8 to
+// 4.5e-8 under the others, against 2e-7 to 3e-7 / 8e-8 to 1e-7 (hi/lo).
 // FP64 frames keep the per-sample sums: the nodes change a pixel by more
 // than their last places.  Strongly bent formats (few pixels per radian of
 // curvature) keep them too: the nodes lie at sample numbers, taken as linear
 // in x.  So do sparse samplings, where a column holds few more samples than nodes: a
 // 4096^2 frame (80 traces, H = 8) takes 0.45 ms at 6 and 0.66 ms at 10 to 60
-// samples a pixel here, against 0.55 (FP64), 0.40 (FP32), 0.36 ms (hi/lo) at
-// 6, 0.92 / 0.65 / 0.59 at 12, 1.00 / 0.73 / 0.67 at 14 and 3.6 / 2.5 / 2.3 at
-// 60 per sample.  Frames of few tiles wait for one tile's chain of traces
+// samples a pixel under the reduced precisions here, against 0.40 (FP32) and
+// 0.36 ms (hi/lo) at 6, 0.65 / 0.59 at 12, 0.73 / 0.67 at 14 and 2.5 / 2.3 at 60
+// per sample.  Frames of few tiles wait for one tile's chain of traces
 // (700^2: 0.10 ms here at 10 to 60 samples a pixel, against 0.09 (FP32) and
 // 0.14 ms (hi/lo) at 20, 0.12 / 0.19 at 30 and 0.19 / 0.34 at 60 per sample;
 // 1500^2, above the line of 768 tiles: 0.17 ms here, 0.16 / 0.12 at 10).  The
-// per-sample FP64 kernel then splits its tiles, so its time goes with tiles
-// times samples a pixel and the line lies where that reaches 6200: here / per
-// sample in us, 300^2 (50 tiles) 98 / 40 at 20 and 114 / 82 at 110 samples a
-// pixel, 700^2 (242) 103 / 92 at 20 and 104 / 117 at 30, 1000^2 (512) 87 / 103
-// at 6 and 122 / 131 at 10, 1500^2 176 / 187 at 10.
+// per-sample FP64 kernel splits the tiles of such frames, so its time goes with tiles
+// times samples a pixel and the line lies where that reaches 9500 (at the least 6
+// samples a pixel): here / per sample under E2E_PREC_F64 in us, 300^2 (50 tiles)
+// 166 / 86 at 110 and 203 / 130 at 200 samples a pixel, 500^2 (128) 137 / 109 at 60
+// and 153 / 162 at 110, 700^2 (242) 127 / 122 at 30 and 131 / 188 at 60, 1000^2 (512)
+// 156 / 145 at 14 and 156 / 171 at 20, 1500^2 (1128) 223 / 206 at 10 and 233 / 247 at
+// 14, 2048^2 192 / 198 at 6, 4096^2 619 / 664 at 6.
 static int sep_fit_nodes(const FormatRes *F, const PsfRes *P, int precision, int out_dtype)
 {
     if (P->kind != E2E_PSF_SEPARABLE || out_dtype != E2E_F32) return 0;
     if (F->ntr > kListTraces || F->bend > 1e-2) return 0;
     const int tiles = ((F->nx + kMfmaTW - 1) / kMfmaTW) * ((F->ny + kMfmaTH - 1) / kMfmaTH);
     const bool few = tiles < kSepFitTiles;
-    const double dense = precision == E2E_PREC_F64   ? (few ? 6200.0 / tiles : 6.0)
+    const double dense = precision == E2E_PREC_F64   ? std::max(9500.0 / tiles, 6.0)
                          : precision == E2E_PREC_F32 ? (few ? 34.0 : 13.0)
                                                      : (few ? 15.0 : 14.0);
     if (F->density < dense) return 0;

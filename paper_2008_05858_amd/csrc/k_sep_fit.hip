@@ -28,8 +28,8 @@
 // tile it reaches, VALU issue in all of the per-sample kernels.  Here a sample
 // costs ~14 FP64 instructions (two mirrored samples share a recurrence; no
 // position: nodes lie at sample numbers) and a tenth as many nodes the pixel
-// integrals: 56.8 ms (FP64 VALU) and 35.0 ms (fp16 hi/lo MFMA) -> 4.9 ms at
-// either precision, still VALU issue, on the node's pixel integrals, the
+// integrals: 56.8 ms (FP64 VALU) -> 5.7 ms, 35.0 ms (fp16 hi/lo MFMA) -> 4.9 ms,
+// still VALU issue, on the node's pixel integrals, the
 // column sums and the FP64 additions of the products.  (With nodes at given x,
 // found by Newton steps, and a position and a full recurrence for each sample
 // it took 5.4 ms.)
@@ -41,11 +41,16 @@
 // per (node, axis) stores the node's pixel integrals on the tile's 64 columns
 // (times photons) or 32 rows as FP32, and finds the next chunk's position and
 // sigma; wave w multiplies column block w, F += Gy diag(Phi) Gx^T, by
-// v_mfma_f32_16x16x4_f32 over 16 nodes at a time, each FP32 partial then added
-// to FP64 sums.  One form serves all precisions: FP64 products
-// (v_mfma_f64_16x16x4_f64) took 6.8 ms where this took 5.4, FP32 sums throughout
-// 5.5 ms, fp16 hi/lo halves 6.4 ms (splitting the weights costs more than the matrix cores
-// save), and this is also the closest to the exact frame of the last three.
+// v_mfma_f32_16x16x4_f32, FP32 partials of SPAN nodes added to FP64 sums: four
+// under E2E_PREC_F64, 16 under the reduced precisions.  A pixel gathers about 30
+// nodes, so a partial of 16 is half of it and its rounding shows: on frames of
+// sigma 0.8 .. 1.6 px the largest error is 1.2e-7 to 1.7e-7 of the peak with 16
+// (C2-shaped frame 4.89 ms), 0.9e-7 to 1.15e-7 with eight (5.17 ms) and 0.65e-7 to
+// 0.99e-7 with four (5.73 ms), where FP64 sums of every sample leave 0.9e-7 to
+// 1.4e-7 (56.4 ms), and the other precisions' per-sample forms 2e-7 (hi/lo) and
+// 1e-6 to 2e-6 (FP32).  FP64 products (v_mfma_f64_16x16x4_f64) took 6.8 ms where
+// 16 took 5.4, fp16 hi/lo halves 6.4 ms (splitting the weights costs more than the
+// matrix cores save).
 // Pixel integrals are taken in FP64: P(z) = 2a phi(z) sum_i A_i (z a)^(2i) /
 // (2i)!, a = h / 2 = 1 / (2 sigma), from exp(-z u) expanded under the integral
 // over the pixel (A_i = int_0^1 v^(2i) exp(-a^2 v^2 / 2) dv by its downward
@@ -208,7 +213,7 @@ struct Vec4<double> {
     }
 };
 
-template <int DX, int DY, typename ST, int M>
+template <int DX, int DY, typename ST, int M, int SPAN>
 __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__restrict__ frames,
                                                            const int2 *__restrict__ work,
                                                            int n_work, int *__restrict__ counter,
@@ -591,7 +596,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                     __syncthreads();
                     if (c0 + CH < nn) prep(c0 + CH + s);
                     // ---- products: wave wv takes column block wv
-                    tile_products<false>(buf, ybuf, nullptr, smask, wv, l16, lg, acc);
+                    tile_products<false, SPAN>(buf, ybuf, nullptr, smask, wv, l16, lg, acc);
                     __syncthreads();
                 }
             }
@@ -601,17 +606,26 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
     }
 }
 
-template <int DX, int DY, typename ST>
-hipError_t launch_st(const FrameDev *frames_dev, int nodes, const int2 *work, int n_work,
-                     int *counter, int *err, int nb, hipStream_t s)
+template <int DX, int DY, typename ST, int M>
+hipError_t launch_m(const FrameDev *frames_dev, int precision, const int2 *work, int n_work,
+                    int *counter, int *err, int nb, hipStream_t s)
 {
-    if (nodes == 10)
-        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, 10>), dim3(nb), dim3(256), 0, s,
+    if (precision == E2E_PREC_F64)
+        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, M, 4>), dim3(nb), dim3(256), 0, s,
                            frames_dev, work, n_work, counter, err);
     else
-        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, 12>), dim3(nb), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, M, 16>), dim3(nb), dim3(256), 0, s,
                            frames_dev, work, n_work, counter, err);
     return hipGetLastError();
+}
+
+template <int DX, int DY, typename ST>
+hipError_t launch_st(const FrameDev *frames_dev, const KernelCfg &cfg, const int2 *work, int n_work,
+                     int *counter, int *err, int nb, hipStream_t s)
+{
+    if (cfg.nodes == 10)
+        return launch_m<DX, DY, ST, 10>(frames_dev, cfg.precision, work, n_work, counter, err, nb, s);
+    return launch_m<DX, DY, ST, 12>(frames_dev, cfg.precision, work, n_work, counter, err, nb, s);
 }
 
 template <int DX, int DY>
@@ -619,8 +633,8 @@ hipError_t launch_deg(const FrameDev *frames_dev, const KernelCfg &cfg, const in
                       int n_work, int *counter, int *err, int nb, hipStream_t s)
 {
     if (cfg.spec_f64)
-        return launch_st<DX, DY, double>(frames_dev, cfg.nodes, work, n_work, counter, err, nb, s);
-    return launch_st<DX, DY, float>(frames_dev, cfg.nodes, work, n_work, counter, err, nb, s);
+        return launch_st<DX, DY, double>(frames_dev, cfg, work, n_work, counter, err, nb, s);
+    return launch_st<DX, DY, float>(frames_dev, cfg, work, n_work, counter, err, nb, s);
 }
 
 }  // namespace

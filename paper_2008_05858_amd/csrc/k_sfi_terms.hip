@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sfi_terms(const FrameDev *__r
                     }
                     __syncthreads();
                     // 4. products
-                    tile_products<true>(buf, ybuf, sscl, smask, wv, l16, lg, acc);
+                    tile_products<true, 16>(buf, ybuf, sscl, smask, wv, l16, lg, acc);
                     __syncthreads();
                 }
             }

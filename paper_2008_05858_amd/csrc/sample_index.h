@@ -8,7 +8,7 @@ namespace e2e {
 // (ks) and the last (ke - 1) sample of a column.
 __host__ __device__ inline double node_sample(int ks, int ke, double tau)
 {
-    return 0.5 * __builtin_fma((double)(ke - 1 - ks), tau, (double)ks + (double)(ke - 1));
+    return 0.5 * __builtin_fma((double)(ke - 1 - ks), tau, (double)((unsigned)ks + (unsigned)(ke - 1)));
 }
 
 // A wave of the table path reads every column's samples as far ahead as its

@@ -131,9 +131,9 @@ __device__ __forceinline__ int tile_traces(const SegDev *segs, int ntr, int ty, 
 }
 
 // The products of one staged chunk: wave wv adds column block wv (rows 4 lg + q
-// of row block rb, column l16) into acc.  SCALED: each node's x row times
-// scl[node].
-template <bool SCALED>
+// of row block rb, column l16) into acc, SPAN nodes (4, 8 or 16) to an FP32 partial.
+// SCALED: each node's x row times scl[node].
+template <bool SCALED, int SPAN>
 __device__ __forceinline__ void tile_products(const float *buf, const float *ybuf, const float *scl,
                                               const unsigned (*smask)[2], int wv, int l16, int lg,
                                               double (*acc)[4])
@@ -157,12 +157,15 @@ __device__ __forceinline__ void tile_products(const float *buf, const float *ybu
             for (int rb = 0; rb < 2; ++rb) {
                 if (!((my >> rb) & 1u)) continue;
                 const f4 av = *reinterpret_cast<const f4 *>(ay + 16 * rb * LS + g);
-                f4 part = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[q], part, 0, 0, 0);
+                for (int p = 0; p < 16 / SPAN; ++p) {
+                    f4 part = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[rb][q] += (double)part[q];
+                    for (int q = p * SPAN / 4; q < (p + 1) * SPAN / 4; ++q)
+                        part = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[q], part, 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[rb][q] += (double)part[q];
+                }
             }
         }
     }
