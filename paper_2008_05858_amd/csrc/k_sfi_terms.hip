@@ -25,13 +25,18 @@
 // it adds up its row (the window sum normalises the sample) and stores the
 // in-tile entries in LDS in operand layout, as k_sep_fit.hip does; each
 // sample's photons over its window sum scale its nodes where the products read
-// them; wave w multiplies column block w, v_mfma_f32_16x16x4_f32 over 16
-// nodes, each FP32 partial added to FP64 sums.  The order of every sum is
-// fixed: the result is deterministic.
+// them; wave w multiplies column block w, v_mfma_f32_16x16x4_f32, FP32 partials
+// of eight nodes added to FP64 sums.  The order of every sum is fixed: the
+// result is deterministic.
 //
-// Measured on that frame: 9.81 -> 1.78 ms, error against 64 bits 4.4e-8 ->
-// 4.0e-8 of the norm; bound by VALU issue on the rows (the y rows twice the x
-// rows).  FP64 products instead of FP32 partials: 2.02 ms, 4.2e-8.
+// Measured on that frame: 9.81 -> 1.84 ms (6.65 -> 1.85 at S = 1, 6.98 -> 1.88 at
+// S = 2: the series do not grow with S, but even one sub-pixel centre costs the
+// image-by-image form 2 R N Gaussians and tails); bound by VALU issue on the rows
+// (the y rows twice the x rows).  Partials of 16 nodes took 1.78 ms and of four 2.01;
+// on 2048^2 frames (S = 1 to 16) their largest error against 64 bits is 1.13e-7 to
+// 1.22e-7 of the peak with 16, 0.94e-7 to 1.10e-7 with eight, 0.91e-7 to 1.05e-7 with
+// four, image by image 1.18e-7 to 1.36e-7; of the norm 4.0e-8, 3.6e-8, 3.5e-8 and
+// 4.5e-8 to 4.7e-8.
 #include "sep_stage.h"
 
 namespace e2e {
@@ -300,7 +305,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sfi_terms(const FrameDev *__r
                     }
                     __syncthreads();
                     // 4. products
-                    tile_products<true, 16>(buf, ybuf, sscl, smask, wv, l16, lg, acc);
+                    tile_products<true, 8>(buf, ybuf, sscl, smask, wv, l16, lg, acc);
                     __syncthreads();
                 }
             }
