@@ -29,11 +29,22 @@ def _frame(psf, n, nx=512, ny=64):
     return f
 
 
-@pytest.mark.parametrize("kind", ["separable"])
+def _table():
+    """Nine round maps, each with its own width."""
+    maps = np.empty((3, 3, 32, 32), np.float32)
+    u = (np.arange(32) - 15.5) / 4.0
+    for q in range(9):
+        g = np.exp(-0.5 * (u / (1.0 + 0.05 * q)) ** 2)
+        maps[q // 3, q % 3] = np.outer(g, g) / g.sum() ** 2
+    return Psf(kind="table", gx=3, gy=3, kw=32, kh=32, tables=maps)
+
+
+@pytest.mark.parametrize("kind", ["separable", "table"])
 @pytest.mark.parametrize("n", [2**30 + 12_345_678, 2**31 - 2])
 def test_the_frame_of_a_thousandth_as_many_samples(kind, n):
     rng = np.random.default_rng(2)
-    psf = Psf(kind="separable", gx=3, gy=3, half_width=6, sigma_xy=rng.uniform(1.0, 1.4, (3, 3, 2)).astype(np.float32))
+    psf = _table() if kind == "table" else Psf(
+        kind="separable", gx=3, gy=3, half_width=6, sigma_xy=rng.uniform(1.0, 1.4, (3, 3, 2)).astype(np.float32))
     print(f"case long {kind} {n}", flush=True)
     a, b = _frame(psf, n), _frame(psf, n // 1000)
     assert b.max() > 0 and abs(a.sum() / b.sum() - 1.0) < 1e-6
