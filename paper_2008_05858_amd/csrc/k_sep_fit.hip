@@ -502,6 +502,12 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                     }
 #pragma unroll
                     for (int p = 0; p < M; ++p) mu[p] = quad_sum(mu[p]);
+                    // a column with an infinite sample: all its nodes are infinite,
+                    // as its samples are one by one
+                    if (fit && __builtin_expect(!isfinite(mu[0]), 0)) {
+#pragma unroll
+                        for (int p = 1; p < M; ++p) mu[p] = 0.0;
+                    }
                     if (fit) {
 #pragma unroll
                         for (int j = 0; j < (M + 3) / 4; ++j) {

@@ -93,6 +93,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sfi_terms(const FrameDev *__r
     __shared__ float sfq[3 * kSfiMaxR];
     __shared__ unsigned short tlist[kMaxTileTraces];
     __shared__ unsigned smask[4][2];
+    __shared__ unsigned long long sh_odd;    // samples whose photons are not ordinary numbers
     __shared__ int sh_item;
     float *const ybuf = buf + TX * LS;
 
@@ -162,6 +163,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sfi_terms(const FrameDev *__r
             for (int kb = sg.k0; kb < sg.k1; kb += PB) {
                 const int nb = min(PB, sg.k1 - kb);
                 // 1. positions, windows, sigmas, photons of up to 64 samples
+                bool odd = false;
                 if (tid < nb) {
                     const int k = kb + tid;
                     const double t = fma((double)k, dt, t0);
@@ -177,6 +179,12 @@ __global__ __launch_bounds__(256, 3) void k_render_sfi_terms(const FrameDev *__r
                     sphi[tid] = (float)(spec_at(spec, k) * scale);
                     sax[tid] = (int)axd - H - X0;
                     say[tid] = (int)ayd - H - Y0;
+                    odd = !(fabsf(sphi[tid]) < 1e30f);
+                }
+                {
+                    static_assert(PB == 64, "the first wave holds them");
+                    const unsigned long long m = __ballot(odd);
+                    if (tid == 0) sh_odd = m;
                 }
                 __syncthreads();
                 // chunks of equal length, each a whole number of samples
@@ -301,11 +309,35 @@ __global__ __launch_bounds__(256, 3) void k_render_sfi_terms(const FrameDev *__r
                         if (tid < nn)
                             for (int p = 0; p < R; ++p)
                                 z = fma(sxs[q * R + p], sys[q * R + p], z);
-                        sscl[tid] = tid < nn ? (float)((double)sphi[c0 + q] * recip(z)) : 0.0f;
+                        const bool use = tid < nn && !((sh_odd >> (c0 + q)) & 1u);
+                        sscl[tid] = use ? (float)((double)sphi[c0 + q] * recip(z)) : 0.0f;
                     }
                     __syncthreads();
                     // 4. products
                     tile_products<true, 8>(buf, ybuf, sscl, smask, wv, l16, lg, acc);
+                    // A NaN, an infinity (or a scale out of FP32's range) stays in
+                    // its own window: the products would carry it to every pixel of
+                    // its blocks of 16, so such a sample is added pixel by pixel.
+                    if (__builtin_expect(uniform_i(sh_odd != 0), 0))
+                        for (int q = 0; q < nk; ++q) {
+                            const int smp = c0 + q;
+                            if (!uniform_i((int)((sh_odd >> smp) & 1u))) continue;
+                            double z = 0.0;
+                            for (int p = 0; p < R; ++p)
+                                z = fma(sxs[q * R + p], sys[q * R + p], z);
+                            const double sc = (double)sphi[smp] / z;
+                            const int col = 16 * wv + l16;
+                            if ((unsigned)(col - sax[smp]) >= (unsigned)N) continue;
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) {
+                                const int row = 16 * (e >> 2) + 4 * lg + (e & 3);
+                                if ((unsigned)(row - say[smp]) >= (unsigned)N) continue;
+                                float v = 0.0f;
+                                for (int p = 0; p < R; ++p)
+                                    v = fmaf(buf[lds_at(col, q * R + p)], ybuf[lds_at(row, q * R + p)], v);
+                                acc[e >> 2][e & 3] = fma((double)v, sc, acc[e >> 2][e & 3]);
+                            }
+                        }
                     __syncthreads();
                 }
             }
