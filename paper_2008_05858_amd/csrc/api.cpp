@@ -148,6 +148,66 @@ static double dpoly(const double *c, int deg, double t, int order)
     return v;
 }
 
+// Bound on the traces that reach one 64 x 32 tile of the column-node path, for
+// any window (half width up to kMaxHalf) and Doppler shift that a request may
+// have: each trace followed over its range of t widened by the largest shift, in
+// steps whose bend is added to their ranges, with the planner's margins.
+static int tile_crowd(const std::vector<TraceDev> &tr, int nx, int ny)
+{
+    constexpr int kMaxHalf = 8, kSteps = 512;
+    const int ntx = (nx + kMfmaTW - 1) / kMfmaTW, nty = (ny + kMfmaTH - 1) / kMfmaTH;
+    std::vector<int> step((size_t)ntx * (nty + 1), 0);  // counts by row, as differences
+    int everywhere = 0;
+    struct Span {
+        double y0, y1, t0, t1;
+    };
+    std::vector<Span> sp(ntx);
+    for (const TraceDev &T : tr) {
+        const double reach = 1.0 + 1e-6 + 2.0 * T.lmax * (1.5e5 / 299792458.0) / (T.lmax - T.lmin);
+        if (!(reach < 2.0)) {
+            ++everywhere;
+            continue;
+        }
+        auto bend = [&](const double *c, int deg) {
+            double b = 0.0;
+            for (int j = 2; j <= deg; ++j) b += j * (j - 1) * fabs(c[j]) * std::pow(reach, j - 2);
+            return b;
+        };
+        const double h = 2.0 * reach / kSteps;
+        const double mx = bend(T.cx, T.degx) * h * h / 8.0 + kMaxHalf + 1.0;
+        const double my = bend(T.cy, T.degy) * h * h / 8.0 + 1e-5;
+        for (Span &s : sp) s = {1e300, -1e300, 1e300, -1e300};
+        double xa = poly(T.cx, T.degx, -reach), ya = poly(T.cy, T.degy, -reach);
+        for (int i = 1; i <= kSteps; ++i) {
+            const double t = -reach + h * i, xb = poly(T.cx, T.degx, t), yb = poly(T.cy, T.degy, t);
+            const double c0 = floor((std::min(xa, xb) - mx) / kMfmaTW), c1 = floor((std::max(xa, xb) + mx) / kMfmaTW);
+            for (int c = (int)std::max(c0, 0.0); c <= std::min(c1, ntx - 1.0); ++c) {
+                Span &s = sp[c];
+                s.y0 = std::min(s.y0, std::min(ya, yb));
+                s.y1 = std::max(s.y1, std::max(ya, yb));
+                s.t0 = std::min(s.t0, t - h);
+                s.t1 = std::max(s.t1, t);
+            }
+            xa = xb;
+            ya = yb;
+        }
+        for (int c = 0; c < ntx; ++c) {
+            const Span &s = sp[c];
+            if (s.y0 > s.y1) continue;
+            const double q = (s.t1 - s.t0) / 8.0, m = my + T.y2max * q * q / 8.0 + kMaxHalf + 2.0;
+            const double r0 = std::max(floor((s.y0 - m) / kMfmaTH), 0.0);
+            const double r1 = std::min(floor((s.y1 + m) / kMfmaTH), nty - 1.0);
+            if (r0 > r1) continue;
+            step[(size_t)c * (nty + 1) + (int)r0] += 1;
+            step[(size_t)c * (nty + 1) + (int)r1 + 1] -= 1;
+        }
+    }
+    int most = 0;
+    for (int c = 0; c < ntx; ++c)
+        for (int r = 0, n = 0; r < nty; ++r) most = std::max(most, n += step[(size_t)c * (nty + 1) + r]);
+    return most + everywhere;
+}
+
 extern "C" e2e_status e2e_format_load(e2e_ctx *ctx, const e2e_trace_desc *tr, int32_t n,
                                       int32_t nx, int32_t ny, e2e_format_id *out)
 {
@@ -244,6 +304,7 @@ extern "C" e2e_status e2e_format_load(e2e_ctx *ctx, const e2e_trace_desc *tr, in
     F->slope = slope;
     F->bend = bend;
     F->density = samples / spans;
+    F->crowd = n <= kMaxTileTraces ? n : tile_crowd(h, nx, ny);
     F->host = h;
     F->bytes = bytes;
     hipError_t e = hipMalloc(&F->dev, bytes);
@@ -626,6 +687,10 @@ static int sep_fit_nodes(const FormatRes *F, const PsfRes *P, int precision, int
 {
     if (P->kind != E2E_PSF_SEPARABLE || out_dtype != E2E_F32) return 0;
     if (F->ntr > kListTraces || F->bend > 1e-2) return 0;
+    // a 64 x 32 tile lists 512 traces; so does a 16 x 16 one of the per-sample FP64
+    // and FP32 kernels, which then take more (the hi/lo ones' tile is this one)
+    const bool hilo = precision == E2E_PREC_BF16_HILO || precision == E2E_PREC_F16_HILO;
+    if (!hilo && F->crowd > kMaxTileTraces) return 0;
     const int tiles = ((F->nx + kMfmaTW - 1) / kMfmaTW) * ((F->ny + kMfmaTH - 1) / kMfmaTH);
     const bool few = tiles < kSepFitTiles;
     const double dense = precision == E2E_PREC_F64   ? std::max(9500.0 / tiles, 6.0)

@@ -22,6 +22,7 @@ struct FormatRes {
     double slope = 0;      // bound on |dy/dx| over the traces
     double density = 0;    // samples per pixel column, mean over the traces
     double bend = 0;       // bound on |x''|, |y''| per pixel (over min(x')^2)
+    int crowd = 0;         // bound on the traces that reach one 64 x 32 tile
     std::vector<TraceDev> host;
     TraceDev *dev = nullptr;
     size_t bytes = 0;
