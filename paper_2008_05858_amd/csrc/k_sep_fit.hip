@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
     __shared__ unsigned short tlist[kMaxTileTraces];
     __shared__ unsigned smask[4][2];
     __shared__ double snode[M];             // tau_m
-    __shared__ int sh_item, sh_nent, sh_raw;
+    __shared__ int sh_item, sh_nent, sh_raw, sh_neg;
     float *const ybuf = buf + TX * LS;       // the rows' lines follow the columns'
 
     const int tid = threadIdx.x;
@@ -265,6 +265,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
         const SegDev *segs = F.segs + (size_t)tx * ntr;
         int count = tile_traces(segs, ntr, ty, tid, smask, tlist, err);
         zero_lines(buf, tid);
+        if (M == 12 && tid == 0) sh_neg = 0;
         __syncthreads();
         int zlo = 1, zhi = 0;  // lines this thread's node slot holds (none)
         double acc[2][4];
@@ -604,6 +605,38 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
                     // ---- products: wave wv takes column block wv
                     tile_products<false, SPAN>(buf, ybuf, nullptr, smask, wv, l16, lg, acc);
                     __syncthreads();
+                }
+            }
+        }
+        // Far from a narrow Gaussian's centre the interpolant can pass below zero, by
+        // 1e-20 of the photons (sigma 0.6 px, isolated bright samples; not with 10
+        // nodes, where sigma is 0.9 px at the least and w varies by e^10 over a column:
+        // the products' rounding shows from e^15).  So where a pixel is negative (rare)
+        // and none of the tile's samples is, it is zero.
+        if constexpr (M == 12) {
+            bool neg = false;
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) neg |= acc[rb][q] < 0.0;
+            if (neg) sh_neg = 1;
+            __syncthreads();
+            if (__builtin_expect(uniform_i(sh_neg) != 0, 0)) {
+                bool meant = false;
+                for (int li = 0; li < count; ++li) {
+                    const int tr = uniform_i((int)tlist[li]);
+                    const ST *spec = (const ST *)F.tf[tr].spec;
+                    const unsigned k1 = segs[tr].k1;
+                    for (unsigned k = (unsigned)segs[tr].k0 + tid; k < k1; k += 256)
+                        meant |= spec[k] < (ST)0;
+                }
+                if (meant) sh_neg = 2;
+                __syncthreads();
+                if (sh_neg == 1) {
+#pragma unroll
+                    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[rb][q] = acc[rb][q] < 0.0 ? 0.0 : acc[rb][q];
                 }
             }
         }
