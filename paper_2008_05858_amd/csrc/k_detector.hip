@@ -50,6 +50,7 @@ __device__ __forceinline__ float normal_f32(double u1, double u2, float *err)
 struct DetArgs {
     double k[9];
     double dark, ron, gain, inv_gain, bias, top;
+    double tiny;   // 1e-14 of the bias and of a step
     uint64_t seed;
     uint32_t fidx;
     int nx, ny;
@@ -104,12 +105,14 @@ __global__ __launch_bounds__(256) void k_detector(const T *__restrict__ frame,
             uniform_pair(a.seed, a.fidx, (uint64_t)p, 0x80000000u, &u1, &u2);
             // the read noise in FP32 first: its ADU is the exact one unless the
             // value lies within the error bound of a step of the ADC, then
-            // (one pixel in about 1e5) it is taken in FP64
+            // (one pixel in about 1e5) it is taken in FP64.  (The roundings of either
+            // form go with the terms, not with their sum: a bias may cancel them.)
             float err;
             const float z = normal_f32(u1, u2, &err);
-            const double t = fma(a.ron * a.inv_gain, (double)z, e * a.inv_gain) + a.bias + 0.5;
+            const double eg = e * a.inv_gain;
+            const double t = fma(a.ron * a.inv_gain, (double)z, eg) + a.bias + 0.5;
             v = floor(t);
-            const double fr = t - v, lim = fma(a.ron * a.inv_gain, (double)err, fma(fabs(t), 1e-14, 1e-14));
+            const double fr = t - v, lim = fma(a.ron * a.inv_gain, (double)err, fma(fabs(eg), 1e-14, a.tiny));
             if (!(fr > lim && fr < 1.0 - lim))
                 v = adc(fma(a.ron, sqrt(-2.0 * log(u1)) * cos(6.283185307179586 * u2), e));
         } else {
@@ -146,6 +149,7 @@ hipError_t launch_detector(const void *frame, int f64, const float *prnu, int nx
     a.ron = ron;
     a.gain = gain;
     a.inv_gain = 1.0 / gain;
+    a.tiny = 1e-14 * (fabs(bias) + 1.0);
     a.bias = bias;
     a.top = (double)((1u << bits) - 1u);
     a.seed = seed;
