@@ -16,16 +16,17 @@ hipError_t launch_smooth3(const void *lt_dev, int n_tmpl, int64_t nmax, int wmax
                           hipStream_t s);
 int loop_max_width();
 bool loop_needs_p(int w);
-int ccf_runs(int nx, int ntr);
+int loop_max_templates();
 hipError_t launch_ccf_mean(const TraceDev *trs, const void *tl_dev, int n_tr, const void *lt_dev,
                            int nx, const double *flux, const double *flat, const double *edges,
                            double v0, double dv, int nv, double *mean, hipStream_t s);
 hipError_t launch_ccf(const TraceDev *trs, const void *tl_dev, int n_tr, int ntr, const void *lt_dev,
                       int nx, double spp, double vspan, const double *flux, const double *flat,
                       const double *edges, double v0, double dv, int nv, const double *mean,
-                      double *part, hipStream_t s);
-hipError_t launch_ccf_sum(const double *part, int ntr, int nx, int nv, double *C, double *tot,
-                          hipStream_t s);
+                      double *part, double *C, hipStream_t s);
+hipError_t launch_ccf_total(const double *part, int ntr, int nx, int nv, double *C, double *tot,
+                            hipStream_t s);
+size_t ccf_part_bytes(int nx, int ntr, int nv);
 size_t loop_template_bytes();
 size_t loop_trace_bytes();
 void loop_template_fill(void *dst, const void *tmpl, double *P, double *X, int64_t n, int w);
@@ -261,11 +262,12 @@ extern "C" e2e_status e2e_ccf(e2e_ctx *ctx, e2e_format_id fmt, const e2e_ccf_req
     const size_t half = ((size_t)nmax + 1) & ~(size_t)1;  // even: the CCF loads 16 bytes
     const size_t stride = half * (wide ? 2 : 1);
     const int nu = (int)uniq.size();
-    const int G = (int)std::max<size_t>(1, std::min<size_t>(nu, ((size_t)192 << 20) / (stride * 8)));
+    const int G = (int)std::max<size_t>(
+        1, std::min<size_t>(std::min(nu, loop_max_templates()), ((size_t)192 << 20) / (stride * 8)));
     auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
     const size_t b_tm = up(nu * loop_template_bytes()), b_tl = up(ntr * loop_trace_bytes());
     const size_t b_mean = up((size_t)ntr * 8), b_tot = up((size_t)nv * 8);
-    const size_t b_C = up((size_t)ntr * nv * 8), b_part = up((size_t)ntr * ccf_runs(nx, ntr) * nv * 8);
+    const size_t b_C = up((size_t)ntr * nv * 8), b_part = up(ccf_part_bytes(nx, ntr, nv));
     KeptBuf kept(ctx);
     if ((e = kept.get(b_tm + b_tl + b_mean + b_tot + b_C + b_part + G * stride * 8)) != hipSuccess)
         return hip_fail(e, "ccf workspace");
@@ -288,6 +290,7 @@ extern "C" e2e_status e2e_ccf(e2e_ctx *ctx, e2e_format_id fmt, const e2e_ccf_req
         e = launch_ccf_mean(F->dev, tl, ntr, tm, nx, fd, fl, ld, r->v0_mps, r->dv_mps, nv, mean, s);
         prof_end(ctx, s);
     }
+    double *const Cout = r->ccf_out && r->on_device ? r->ccf_out : Cd;
     at = 0;
     for (int u0 = 0; u0 < nu && e == hipSuccess; u0 += G) {
         const int g = std::min(G, nu - u0);
@@ -311,13 +314,12 @@ extern "C" e2e_status e2e_ccf(e2e_ctx *ctx, e2e_format_id fmt, const e2e_ccf_req
         if (e != hipSuccess) break;
         prof_begin(ctx, s, "ccf");
         e = launch_ccf(F->dev, tl + at * loop_trace_bytes(), nt, ntr, tm, nx, spp, vspan, fd, fl, ld,
-                       r->v0_mps, r->dv_mps, nv, mean, part, s);
+                       r->v0_mps, r->dv_mps, nv, mean, part, Cout, s);
         prof_end(ctx, s);
         at += nt;
     }
     // the sums over the columns' runs and over the traces, each in order
-    double *const Cout = r->ccf_out && r->on_device ? r->ccf_out : Cd;
-    if (e == hipSuccess) e = launch_ccf_sum(part, ntr, nx, nv, Cout, tot_d, s);
+    if (e == hipSuccess) e = launch_ccf_total(part, ntr, nx, nv, Cout, tot_d, s);
     std::vector<double> tot(nv);
     if (e == hipSuccess) e = hipMemcpyAsync(tot.data(), tot_d, nv * 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && r->ccf_out && !r->on_device)

@@ -13,7 +13,7 @@
 //    the window is narrow, from registers and one LDS array of prefix sums,
 //    else one launch per pass.  Traces that share a template and a width (the
 //    slices of a fiber) share its smoothed copy.
-//  * k_ccf_mean / k_ccf / k_ccf_sum: the mean of the flat-divided flux over
+//  * k_ccf_mean / k_ccf / k_ccf_sum (k_ccf_runs and k_ccf_total): the mean of the flat-divided flux over
 //    the usable columns; then a workgroup per (trace, run of columns) stages
 //    the stretch of the smoothed template that a few columns read under every
 //    trial velocity in LDS and adds up all velocities from there (linear
@@ -339,7 +339,8 @@ __global__ __launch_bounds__(KT) void k_ccf(const TraceDev *__restrict__ trs,
                                             int step, const double *__restrict__ flux,
                                             const double *__restrict__ flat,
                                             const double *__restrict__ edges, double v0, double dv,
-                                            int nv, const double *__restrict__ mean,
+                                            int nv, int k0, int kn_all, int by_trace,
+                                            const double *__restrict__ mean,
                                             double *__restrict__ part)
 {
     typedef double d2 __attribute__((ext_vector_type(2)));
@@ -360,10 +361,11 @@ __global__ __launch_bounds__(KT) void k_ccf(const TraceDev *__restrict__ trs,
     __syncthreads();
     // threads share the velocities of a turn of up to KT: `ways` threads a
     // velocity, each every ways-th column
-    double *const out = part + ((size_t)me.trace * gridDim.x + blockIdx.x) * nv;
-    for (int kb = 0; kb < nv; kb += KT) {
-        const int kn = min(KT, nv - kb), ways = KT / kn;
-        const int k = kb + tid % kn, way = tid / kn;
+    double *const out =
+        part + ((size_t)(by_trace ? me.trace : (int)blockIdx.y) * gridDim.x + blockIdx.x) * kn_all;
+    for (int kb = 0; kb < kn_all; kb += KT) {
+        const int kn = min(KT, kn_all - kb), ways = KT / kn;
+        const int k = k0 + kb + tid % kn, way = tid / kn;
         const double d = 1.0 + (v0 + k * dv) / 299792458.0, g = 1.0 / d;
         double acc = 0.0;
         for (int c0 = 0; c0 < cols; c0 += step) {
@@ -448,6 +450,37 @@ __global__ __launch_bounds__(256) void k_ccf_sum(const double *__restrict__ part
     if (tid == 0) tot[k] = red[0];
 }
 
+// The same in two kernels, where the partial sums of all traces and velocities are
+// too many to hold: ccf[tr][k0 + k] of a launch's traces and velocities,
+__global__ __launch_bounds__(256) void k_ccf_runs(const double *__restrict__ part,
+                                                  const LoopTrace *__restrict__ tl, int runs, int nv,
+                                                  int k0, int kn, double *__restrict__ C)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= kn) return;
+    const double *p = part + (size_t)blockIdx.y * runs * kn + k;
+    double s = 0.0;
+    for (int r = 0; r < runs; ++r) s += p[(size_t)r * kn];
+    C[(size_t)tl[blockIdx.y].trace * nv + k0 + k] = s;
+}
+
+// and at the end the sum over the traces.
+__global__ __launch_bounds__(256) void k_ccf_total(const double *__restrict__ C, int ntr, int nv, int k0,
+                                                   double *__restrict__ tot)
+{
+    __shared__ double red[256];
+    const int k = k0 + blockIdx.x, tid = threadIdx.x;
+    double all = 0.0;
+    for (int t = tid; t < ntr; t += 256) all += C[(size_t)t * nv + k];
+    red[tid] = all;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (tid < o) red[tid] += red[tid + o];
+        __syncthreads();
+    }
+    if (tid == 0) tot[k] = red[0];
+}
+
 }  // namespace
 
 hipError_t launch_extract(const TraceDev *trs, int ntr, int nx, int ny, const void *frame,
@@ -465,7 +498,10 @@ hipError_t launch_extract(const TraceDev *trs, int ntr, int nx, int ny, const vo
 }
 
 bool loop_needs_p(int w);
+constexpr int kGridY = 65535;   // workgroups of a launch's second dimension
+int loop_max_templates() { return kGridY; }
 
+// (n_tmpl at most loop_max_templates())
 hipError_t launch_smooth3(const void *lt_dev, int n_tmpl, int64_t nmax, int wmax, int f64,
                           hipStream_t s)
 {
@@ -509,28 +545,75 @@ hipError_t launch_ccf_mean(const TraceDev *trs, const void *tl_dev, int n_tr, co
     return hipGetLastError();
 }
 
-// n_tr of the format's ntr traces; step: columns whose reads are expected to
-// fit LDS, for templates of at most `spp` samples a column and a velocity grid
-// of `vspan` samples
+// Partial sums at a time (bytes), and the velocities of a launch: longer grids go
+// slice by slice (whole turns of KT: a velocity's sum is the same in any slice).
+// Where the sums of all traces fit, one kernel at the end adds them up (with eight
+// groups of templates 2.56 ms against 2.61 for a kernel after each group).
+constexpr size_t kCcfPart = (size_t)128 << 20;
+constexpr int kCcfSlice = 8 * KT;
+static size_t ccf_trace_bytes(int nx, int ntr, int nv)
+{
+    return (size_t)ccf_runs(nx, ntr) * (nv < kCcfSlice ? nv : kCcfSlice) * sizeof(double);
+}
+static int ccf_traces(int nx, int ntr, int nv)   // of a launch
+{
+    const size_t fit = kCcfPart / ccf_trace_bytes(nx, ntr, nv);
+    return (int)(fit < 1 ? 1 : fit < (size_t)kGridY ? fit : (size_t)kGridY);
+}
+static bool ccf_whole(int nx, int ntr, int nv) { return nv <= kCcfSlice && ntr <= ccf_traces(nx, ntr, nv); }
+size_t ccf_part_bytes(int nx, int ntr, int nv)
+{
+    const int most = ccf_traces(nx, ntr, nv);
+    return (ntr < most ? ntr : most) * ccf_trace_bytes(nx, ntr, nv);
+}
+
+// n_tr of the format's ntr traces, their partial sums or their rows of C (see
+// ccf_whole); step: columns whose reads are
+// expected to fit LDS, for templates of at most `spp` samples a column and a
+// velocity grid of `vspan` samples
 hipError_t launch_ccf(const TraceDev *trs, const void *tl_dev, int n_tr, int ntr, const void *lt_dev,
                       int nx, double spp, double vspan, const double *flux, const double *flat,
                       const double *edges, double v0, double dv, int nv, const double *mean,
-                      double *part, hipStream_t s)
+                      double *part, double *C, hipStream_t s)
 {
-    if (n_tr <= 0) return hipSuccess;
     const double fit = (KX - 8 - vspan) / (spp > 1e-6 ? spp : 1e-6);
     const int step = fit >= KS ? KS : fit >= 4.0 ? (int)fit : KS;
-    hipLaunchKernelGGL(k_ccf, dim3(ccf_runs(nx, ntr), n_tr), dim3(KT), 0, s, trs,
-                       (const LoopTrace *)tl_dev, (const LoopTemplate *)lt_dev, nx, ccf_run(nx, ntr),
-                       step, flux, flat, edges, v0, dv, nv, mean, part);
-    return hipGetLastError();
+    const int runs = ccf_runs(nx, ntr), most = ccf_traces(nx, ntr, nv);
+    const bool whole = ccf_whole(nx, ntr, nv);
+    for (int t = 0; t < n_tr; t += most) {
+        const int n = n_tr - t < most ? n_tr - t : most;
+        const LoopTrace *tl = (const LoopTrace *)tl_dev + t;
+        for (int k0 = 0; k0 < nv;) {
+            const int kn = nv - k0 < kCcfSlice ? nv - k0 : kCcfSlice;
+            hipLaunchKernelGGL(k_ccf, dim3(runs, n), dim3(KT), 0, s, trs, tl, (const LoopTemplate *)lt_dev,
+                               nx, ccf_run(nx, ntr), step, flux, flat, edges, v0, dv, nv, k0, kn, (int)whole, mean,
+                               part);
+            if (!whole)
+                hipLaunchKernelGGL(k_ccf_runs, dim3((kn + 255) / 256, n), dim3(256), 0, s, part, tl, runs,
+                                   nv, k0, kn, C);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            k0 += kn;
+        }
+    }
+    return hipSuccess;
 }
 
-hipError_t launch_ccf_sum(const double *part, int ntr, int nx, int nv, double *C, double *tot,
-                          hipStream_t s)
+hipError_t launch_ccf_total(const double *part, int ntr, int nx, int nv, double *C, double *tot,
+                            hipStream_t s)
 {
-    hipLaunchKernelGGL(k_ccf_sum, dim3(nv), dim3(256), 0, s, part, ccf_runs(nx, ntr), ntr, nv, C, tot);
-    return hipGetLastError();
+    if (ccf_whole(nx, ntr, nv)) {
+        hipLaunchKernelGGL(k_ccf_sum, dim3(nv), dim3(256), 0, s, part, ccf_runs(nx, ntr), ntr, nv, C, tot);
+        return hipGetLastError();
+    }
+    for (int k0 = 0; k0 < nv;) {
+        const int kn = nv - k0 < (1 << 20) ? nv - k0 : 1 << 20;
+        hipLaunchKernelGGL(k_ccf_total, dim3(kn), dim3(256), 0, s, C, ntr, nv, k0, tot);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        k0 += kn;
+    }
+    return hipSuccess;
 }
 
 size_t loop_template_bytes() { return sizeof(LoopTemplate); }
