@@ -189,7 +189,10 @@ typedef struct {
 } e2e_serve_config;
 
 /* Context bound to one HIP device; hbm_budget_bytes caps the device memory
- * that resident tables plus in-flight renders may use (0 = 90% of free). */
+ * that resident tables plus in-flight renders may use (0 = 90% of free).
+ * Workspaces that the library keeps between calls (e2e_ccf's, and the partial
+ * sums of small frames' split tiles, up to 100 MB a stream) stay within what
+ * the budget leaves and are given back when a call needs their room. */
 e2e_status e2e_create(e2e_ctx **out, int32_t hip_device, uint64_t hbm_budget_bytes);
 /* Drains the serve loop, frees every resident table. */
 void e2e_destroy(e2e_ctx *ctx);
@@ -401,8 +404,9 @@ e2e_status e2e_extract(e2e_ctx *ctx, e2e_format_id fmt, const void *frame, int32
  * (templates is still a host array of n_templates pointers).  ccf_out may
  * be NULL.  The library needs up to 192 MB of smoothed templates at a
  * time (n FP64 values per template in use, 2 n for windows above 1025 samples;
- * at least one) and partial sums; the context keeps a workspace of up to 256 MB
- * between calls, larger ones are allocated for the call.
+ * at least one) and up to 128 MB of partial sums; the context keeps a workspace of
+ * up to 256 MB between calls where its budget has the room, others are allocated
+ * for the call.
  * Errors: E2E_EINVAL (NULL pointers, n_v < 3, dv = 0, smooth_px <= 0, a
  * moving-mean width above 4095 samples, too few templates, bad dtype),
  * E2E_ENOTFOUND, E2E_ENOMEM, E2E_EDEVICE.

@@ -81,6 +81,45 @@ extern "C" e2e_status e2e_create(e2e_ctx **out, int32_t dev, uint64_t budget)
     return E2E_OK;
 }
 
+static void release_kept(e2e_ctx *ctx)
+{
+    if (ctx->kept == 0) return;
+    hipDeviceSynchronize();  // launches in flight may use them
+    hipFree(ctx->loop_ws);
+    ctx->loop_ws = nullptr;
+    ctx->loop_cap = 0;
+    for (auto &kv : ctx->scratch) {
+        hipFree(kv.second->parts);
+        kv.second->parts = nullptr;
+        kv.second->parts_cap = 0;
+    }
+    ctx->kept = 0;
+}
+
+bool e2e::fits_beside(const e2e_ctx *ctx, size_t need)
+{
+    return ctx->used + ctx->in_flight + ctx->kept + need <= ctx->budget;
+}
+
+void e2e::make_room(e2e_ctx *ctx, size_t need)
+{
+    if (!fits_beside(ctx, need)) release_kept(ctx);
+}
+
+hipError_t e2e::dev_malloc(e2e_ctx *ctx, void **p, size_t bytes, bool locked)
+{
+    *p = nullptr;
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    std::unique_lock<std::mutex> lk(ctx->mu, std::defer_lock);
+    if (!locked) lk.lock();
+    if (ctx->kept == 0) return e;
+    release_kept(ctx);
+    *p = nullptr;
+    return hipMalloc(p, bytes);
+}
+
 static void free_scratch(Scratch *s)
 {
     if (!s) return;
@@ -289,11 +328,13 @@ extern "C" e2e_status e2e_format_load(e2e_ctx *ctx, const e2e_trace_desc *tr, in
         dym = std::max(dym, T.degy);
         nslots = std::max(nslots, T.slot + 1);
     }
+    const int crowd = n <= kMaxTileTraces ? n : tile_crowd(h, nx, ny);
     hipSetDevice(ctx->dev);
     size_t bytes = sizeof(TraceDev) * n;
     std::lock_guard<std::mutex> lk(ctx->mu);
     if (ctx->used + bytes > ctx->budget)
         return fail(E2E_ENOMEM, "e2e_format_load: %zu bytes exceed the HBM budget", bytes);
+    make_room(ctx, bytes);
     auto *F = new FormatRes();
     F->nx = nx;
     F->ny = ny;
@@ -304,10 +345,10 @@ extern "C" e2e_status e2e_format_load(e2e_ctx *ctx, const e2e_trace_desc *tr, in
     F->slope = slope;
     F->bend = bend;
     F->density = samples / spans;
-    F->crowd = n <= kMaxTileTraces ? n : tile_crowd(h, nx, ny);
+    F->crowd = crowd;
     F->host = h;
     F->bytes = bytes;
-    hipError_t e = hipMalloc(&F->dev, bytes);
+    hipError_t e = dev_malloc(ctx, (void **)&F->dev, bytes, true);
     if (e == hipSuccess) e = hipMemcpy(F->dev, h.data(), bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         hipFree(F->dev);
@@ -518,20 +559,21 @@ extern "C" e2e_status e2e_psf_load(e2e_ctx *ctx, const e2e_psf_desc *d, e2e_psf_
     size_t bytes = frag.size() * sizeof(uint16_t) + (sxy.size() + sfq.size()) * sizeof(float);
     std::lock_guard<std::mutex> lk(ctx->mu);
     if (ctx->used + bytes > ctx->budget) return bad(E2E_ENOMEM, "tables exceed the HBM budget");
+    make_room(ctx, bytes);
     hipError_t e = hipSuccess;
     if (!frag.empty()) {
-        e = hipMalloc(&P->tfrag, frag.size() * sizeof(uint16_t));
+        e = dev_malloc(ctx, (void **)&P->tfrag, frag.size() * sizeof(uint16_t), true);
         if (e == hipSuccess)
             e = hipMemcpy(P->tfrag, frag.data(), frag.size() * sizeof(uint16_t),
                           hipMemcpyHostToDevice);
     }
     if (e == hipSuccess && !sxy.empty()) {
-        e = hipMalloc(&P->sxy, sxy.size() * sizeof(float));
+        e = dev_malloc(ctx, (void **)&P->sxy, sxy.size() * sizeof(float), true);
         if (e == hipSuccess)
             e = hipMemcpy(P->sxy, sxy.data(), sxy.size() * sizeof(float), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess && !sfq.empty()) {
-        e = hipMalloc(&P->sfq, sfq.size() * sizeof(float));
+        e = dev_malloc(ctx, (void **)&P->sfq, sfq.size() * sizeof(float), true);
         if (e == hipSuccess)
             e = hipMemcpy(P->sfq, sfq.data(), sfq.size() * sizeof(float), hipMemcpyHostToDevice);
     }
@@ -588,12 +630,12 @@ extern "C" e2e_status e2e_psf_free(e2e_ctx *ctx, e2e_psf_id id)
 
 // ------------------------------------------------------------ render core
 
-static e2e_status grow(void **p, size_t *cap, size_t need, const char *what)
+static e2e_status grow(e2e_ctx *ctx, void **p, size_t *cap, size_t need, const char *what)
 {
     if (*cap >= need) return E2E_OK;
     size_t n = std::max(need, *cap * 2);
     void *q = nullptr;
-    hipError_t e = hipMalloc(&q, n);
+    hipError_t e = dev_malloc(ctx, &q, n, true);
     if (e != hipSuccess) return hip_fail(e, what);
     hipFree(*p);
     *p = q;
@@ -833,6 +875,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
     if (ctx->used + temp_bytes + scratch_need > ctx->budget)
         return fail(E2E_ENOMEM, "render needs %zu bytes beyond the %llu-byte budget",
                     temp_bytes + scratch_need, (unsigned long long)ctx->budget);
+    if (!noalloc) make_room(ctx, temp_bytes + scratch_need);
     e2e_status st;
     if (noalloc) {
         // [err, counter | frame record | spectrum pointers | planner output]
@@ -851,16 +894,16 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         sc->segs = reinterpret_cast<SegDev *>(ctx->noalloc.base + o_seg);
     }
     // planner output: segments of every frame, then the per-trace constants
-    if (!noalloc && (st = grow((void **)&sc->segs, &sc->segs_cap, seg_bytes + 16, "segs")) != E2E_OK)
+    if (!noalloc && (st = grow(ctx, (void **)&sc->segs, &sc->segs_cap, seg_bytes + 16, "segs")) != E2E_OK)
         return st;
     if (!noalloc) {
-        if ((st = grow((void **)&sc->frames_dev, &sc->frames_cap, n * sizeof(FrameDev),
+        if ((st = grow(ctx, (void **)&sc->frames_dev, &sc->frames_cap, n * sizeof(FrameDev),
                        "frames")) != E2E_OK)
             return st;
-        if ((st = grow((void **)&sc->work, &sc->work_cap, work_n * sizeof(int2) + 16, "work")) !=
+        if ((st = grow(ctx, (void **)&sc->work, &sc->work_cap, work_n * sizeof(int2) + 16, "work")) !=
             E2E_OK)
             return st;
-        if ((st = grow((void **)&sc->specptrs, &sc->specptrs_cap,
+        if ((st = grow(ctx, (void **)&sc->specptrs, &sc->specptrs_cap,
                        nslots_total * sizeof(void *) + 16, "spectra")) != E2E_OK)
             return st;
     }
@@ -872,12 +915,29 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         (kind == E2E_PSF_SEPARABLE && prec == E2E_PREC_F64))
         for (int i = 0; i < n; ++i) sep_items += nodes[i] == 0 ? tiles[i] : 0;
     const size_t part_bytes = sep_items * kSepUnits * 256 * sizeof(double);
-    if (!noalloc && sep_items > 0 && sep_items <= kSepSplitItems &&
-        ctx->used + temp_bytes + scratch_need + part_bytes + sep_items * sizeof(int) <= ctx->budget) {
-        if (grow(&sc->parts, &sc->parts_cap, part_bytes + sep_items * sizeof(int), "units") == E2E_OK)
+    if (!noalloc && sep_items > 0 && sep_items <= kSepSplitItems) {
+        const size_t need = part_bytes + sep_items * sizeof(int);
+        const size_t more = need > sc->parts_cap ? need - sc->parts_cap : 0;
+        if (more > 0 && ctx->loop_ws && !fits_beside(ctx, temp_bytes + scratch_need + more)) {
+            ctx->kept -= ctx->loop_cap;   // (idle: its call's stream has passed)
+            hipFree(ctx->loop_ws);
+            ctx->loop_ws = nullptr;
+            ctx->loop_cap = 0;
+        }
+        if (more > 0 && fits_beside(ctx, temp_bytes + scratch_need + more)) {
+            ctx->kept -= sc->parts_cap;
+            hipFree(sc->parts);
+            sc->parts_cap = 0;
+            if (hipMalloc(&sc->parts, need) == hipSuccess) {
+                sc->parts_cap = need;
+                ctx->kept += need;
+            } else {
+                sc->parts = nullptr;
+                (void)hipGetLastError();  // no memory for them: without
+            }
+        }
+        if (sc->parts_cap >= need)
             cfg.parts = {reinterpret_cast<int *>((char *)sc->parts + part_bytes), (double *)sc->parts};
-        else
-            (void)hipGetLastError();  // no memory for them: without
     }
 
     // spectra pointers (device), host spectra copied to temporaries
@@ -893,7 +953,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
                 continue;
             }
             void *d = nullptr;
-            if ((e = hipMalloc(&d, len[q] * esz)) != hipSuccess) return hip_fail(e, "spectrum");
+            if ((e = dev_malloc(ctx, &d, len[q] * esz, true)) != hipSuccess) return hip_fail(e, "spectrum");
             sc->temps.push_back(d);
             if ((e = hipMemcpyAsync(d, r.spectra[q], len[q] * esz, hipMemcpyHostToDevice, s)) !=
                 hipSuccess)
@@ -916,7 +976,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
             dev_out[i] = r.out;
         } else {
             size_t ob = (size_t)fm->nx * fm->ny * (r.out_dtype == E2E_F64 ? 8 : 4);
-            if ((e = hipMalloc(&dev_out[i], ob)) != hipSuccess) return hip_fail(e, "out");
+            if ((e = dev_malloc(ctx, &dev_out[i], ob, true)) != hipSuccess) return hip_fail(e, "out");
             sc->temps.push_back(dev_out[i]);
         }
         F.out = dev_out[i];
@@ -1324,7 +1384,7 @@ extern "C" e2e_status e2e_noise_poisson(e2e_ctx *ctx, void *frame, int32_t dtype
     void *d = frame;
     hipError_t e;
     if (!on_device) {
-        if ((e = hipMalloc(&d, bytes)) != hipSuccess) return hip_fail(e, "noise buffer");
+        if ((e = dev_malloc(ctx, &d, bytes, false)) != hipSuccess) return hip_fail(e, "noise buffer");
         if ((e = hipMemcpyAsync(d, frame, bytes, hipMemcpyHostToDevice, s)) != hipSuccess) {
             hipFree(d);
             return hip_fail(e, "noise upload");
@@ -1374,7 +1434,7 @@ extern "C" e2e_status e2e_detector(e2e_ctx *ctx, const e2e_detector_desc *d, con
         // staged copies of the caller's host buffers
         const size_t off_g = (fbytes + 255) & ~(size_t)255;
         const size_t off_o = off_g + ((gbytes + 255) & ~(size_t)255);
-        if ((e = hipMalloc((void **)&blk, off_o + obytes)) != hipSuccess)
+        if ((e = dev_malloc(ctx, (void **)&blk, off_o + obytes, false)) != hipSuccess)
             return hip_fail(e, "detector buffers");
         fd = blk;
         gd = prnu ? (const float *)(blk + off_g) : nullptr;

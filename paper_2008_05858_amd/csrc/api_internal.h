@@ -124,6 +124,12 @@ struct e2e_ctx {
     std::map<std::string, e2e::TuneRec> tune;  // by workload shape (guarded by mu)
     void *loop_ws = nullptr;      // a CCF's workspace, kept between calls (guarded by mu)
     size_t loop_cap = 0;
+    // Bytes of the workspaces kept for later calls (loop_ws, every Scratch's parts;
+    // guarded by mu).  Together with `used` and the served requests in flight they
+    // stay within the budget, but they refuse nothing: a load or render that needs
+    // their room, or memory that the device has not, gets it (make_room, dev_malloc).
+    size_t kept = 0;
+    std::atomic<uint64_t> in_flight{0};   // footprints of the admitted served requests
     std::mutex srv_mu;
 };
 
@@ -132,6 +138,13 @@ namespace e2e {
 e2e_status fail(e2e_status code, const char *fmt, ...);
 e2e_status hip_fail(hipError_t e, const char *what);
 double now_us(const e2e_ctx *ctx);
+// Gives the kept workspaces back if they and `need` more bytes exceed the budget.
+// The caller holds mu.
+void make_room(e2e_ctx *ctx, size_t need);
+bool fits_beside(const e2e_ctx *ctx, size_t need);   // (mu held)
+// hipMalloc, once more without the kept workspaces if the device is full (`locked`:
+// the caller holds mu).
+hipError_t dev_malloc(e2e_ctx *ctx, void **p, size_t bytes, bool locked);
 Scratch *scratch_for(e2e_ctx *ctx, hipStream_t s);
 e2e_status validate_req(e2e_ctx *ctx, const e2e_render_req *r, FormatRes **pf, PsfRes **pp);
 // Render n frames (batch: one persistent launch).  Caller must not hold mu.

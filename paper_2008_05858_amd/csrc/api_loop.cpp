@@ -39,25 +39,26 @@ namespace {
 
 // Device buffers of one call, released on every exit path.
 struct Bufs {
+    e2e_ctx *ctx;
     std::vector<void *> p;
+    explicit Bufs(e2e_ctx *c) : ctx(c) {}
     ~Bufs()
     {
         for (void *q : p) hipFree(q);
     }
     hipError_t get(void **out, size_t bytes)
     {
-        *out = nullptr;
-        hipError_t e = hipMalloc(out, bytes > 0 ? bytes : 16);
+        hipError_t e = dev_malloc(ctx, out, bytes > 0 ? bytes : 16, false);
         if (e == hipSuccess) p.push_back(*out);
         return e;
     }
 };
 
-// The workspace of a CCF, kept by the context between calls: one buffer of at
-// most kLoopKeep bytes, taken by a call and put back when its stream has passed
-// its kernels (a call that finds none, as beside another one, allocates its own).
-// Allocating 200 MB and freeing it (which waits for the whole device) took 0.4 ms
-// of a 3.0 ms call.
+// The workspace of a CCF, kept by the context between calls where its budget has
+// the room: one buffer of at most kLoopKeep bytes, taken by a call and put back when
+// its stream has passed its kernels (a call that finds none, as beside another one,
+// allocates its own).  Allocating 200 MB and freeing it (which waits for the whole
+// device) took 0.4 ms of a 3.0 ms call.
 constexpr size_t kLoopKeep = (size_t)256 << 20;
 struct KeptBuf {
     e2e_ctx *ctx;
@@ -67,24 +68,25 @@ struct KeptBuf {
     KeptBuf(const KeptBuf &) = delete;
     hipError_t get(size_t need)
     {
-        void *small = nullptr;
         {
             std::lock_guard<std::mutex> lk(ctx->mu);
             std::swap(p, ctx->loop_ws);
             std::swap(cap, ctx->loop_cap);
+            ctx->kept -= cap;
         }
         if (p && cap >= need) return hipSuccess;
-        std::swap(p, small);
-        if (small) hipFree(small);
+        if (p) hipFree(p);
+        p = nullptr;
         cap = need;
-        return hipMalloc(&p, need);
+        return dev_malloc(ctx, &p, need, false);
     }
     ~KeptBuf()
     {
         if (!p) return;
         if (cap <= kLoopKeep) {
             std::lock_guard<std::mutex> lk(ctx->mu);
-            if (ctx->loop_cap < cap || !ctx->loop_ws) {
+            if (!ctx->loop_ws && fits_beside(ctx, cap)) {
+                ctx->kept += cap;
                 std::swap(p, ctx->loop_ws);
                 std::swap(cap, ctx->loop_cap);
             }
@@ -138,7 +140,7 @@ extern "C" e2e_status e2e_extract(e2e_ctx *ctx, e2e_format_id fmt, const void *f
     hipStream_t s = stream ? (hipStream_t)stream : ctx->stream;
     const size_t npx = (size_t)F->nx * F->ny, fb = npx * (dtype == E2E_F64 ? 8 : 4);
     const size_t eb = (size_t)F->ntr * F->nx * 8, lb = (size_t)F->ntr * (F->nx + 1) * 8;
-    Bufs B;
+    Bufs B(ctx);
     const void *fd = frame;
     double *ed = flux, *ld = edges;
     hipError_t e = hipSuccess;
@@ -189,7 +191,7 @@ extern "C" e2e_status e2e_ccf(e2e_ctx *ctx, e2e_format_id fmt, const e2e_ccf_req
     const int ntr = F->ntr, nx = F->nx, nv = r->n_v;
     const size_t esz = r->template_dtype == E2E_F64 ? 8 : 4;
     const size_t eb = (size_t)ntr * nx * 8, lb = (size_t)ntr * (nx + 1) * 8;
-    Bufs B;
+    Bufs B(ctx);
     hipError_t e = hipSuccess;
     const double *fd = r->flux, *fl = r->flat, *ld = r->edges;
     std::vector<const void *> tmpl(F->nslots, nullptr);

@@ -91,18 +91,20 @@ static void finish(e2e_ctx *ctx, Server *S, SReq *q, e2e_status st, const std::s
     q->status = st;
     q->done = true;
     S->reserved -= q->footprint;
+    ctx->in_flight = S->reserved;
     S->admitted -= 1;
 }
 
 // Upload host spectra and allocate device (and pinned) frames for an
 // admitted request; called without S->m held.
-static e2e_status stage_in(SReq *q, hipStream_t s)
+static e2e_status stage_in(e2e_ctx *ctx, SReq *q, hipStream_t s)
 {
     hipError_t e;
     for (size_t i = 0; i < q->specs.size(); ++i) {
         if (q->r.spectra_on_device || !q->host_stage[i]) continue;
         void *d = nullptr;
-        if ((e = hipMalloc(&d, q->spec_bytes[i])) != hipSuccess) return hip_fail(e, "serve spectra");
+        if ((e = dev_malloc(ctx, &d, q->spec_bytes[i], false)) != hipSuccess)
+            return hip_fail(e, "serve spectra");
         q->dev_owned.push_back(d);
         if ((e = hipMemcpyAsync(d, q->host_stage[i], q->spec_bytes[i], hipMemcpyHostToDevice, s)) !=
             hipSuccess)
@@ -111,7 +113,7 @@ static e2e_status stage_in(SReq *q, hipStream_t s)
     }
     if (!q->r.out_on_device) {
         void *d = nullptr;
-        if ((e = hipMalloc(&d, q->out_bytes)) != hipSuccess) return hip_fail(e, "serve frame");
+        if ((e = dev_malloc(ctx, &d, q->out_bytes, false)) != hipSuccess) return hip_fail(e, "serve frame");
         q->dev_owned.push_back(d);
         q->r.out = d;
         if ((e = hipHostMalloc(&q->out_stage, q->out_bytes)) != hipSuccess) {
@@ -231,6 +233,11 @@ static void loop(e2e_ctx *ctx, Server *S)
             }
             std::vector<SReq *> group = take_group(ctx, S, avail);
             if (group.empty()) break;
+            {
+                std::lock_guard<std::mutex> g(ctx->mu);
+                ctx->in_flight = S->reserved;
+                make_room(ctx, 0);
+            }
             S->stream_busy[si] = true;
             Flight f;
             f.stream = si;
@@ -239,7 +246,7 @@ static void loop(e2e_ctx *ctx, Server *S)
             lk.unlock();
             std::vector<e2e_render_req> rr;
             for (SReq *q : group) {
-                e2e_status st = stage_in(q, s);
+                e2e_status st = stage_in(ctx, q, s);
                 if (st != E2E_OK) f.launch_status = st;
                 rr.push_back(q->r);
             }
