@@ -282,9 +282,11 @@ e2e_status e2e_serve_stop(e2e_ctx *ctx);
  * Launch autotuner (the batch / serve orchestration of Sec. 3, sized to one
  * GPU).  Renders the given requests (n = 1: the plain renderer; n > 1: one
  * persistent batch launch) under each candidate launch choice -- work-unit
- * length in tiles (table path: 2, 4, 8, 16) and, for batches, persistent
- * workgroups per CU (1..3) -- times them with HIP events (a warm-up run,
- * then the best of two), and keeps the fastest for the requests' workload
+ * length in tiles (table path: 2, 4, 8, 16 and the frames' default, reported
+ * as 0 where the requests' defaults differ) and, for batches of the table
+ * path, persistent workgroups per CU (1..3) -- times them with HIP events (a
+ * warm-up run, then the best of two), and keeps the fastest (the default on a
+ * tie) for the requests' workload
  * shapes (PSF kind and grid, precision, spectrum type, detector size, trace
  * count and degrees).  Later e2e_render, e2e_render_batch and served
  * requests of those shapes use it.  The requests' outputs are written by

@@ -1275,6 +1275,7 @@ extern "C" e2e_status e2e_autotune(e2e_ctx *ctx, const e2e_render_req *reqs, int
     if (!ctx || !reqs || n < 1) return fail(E2E_EINVAL, "e2e_autotune: bad arguments");
     std::vector<std::string> keys(n);
     bool table = false;
+    int usual = 0;  // the default unit length, if the requests share one
     {
         // handles are looked up under the context lock; run_frames takes it
         // again for each timed run, so it is not held across them
@@ -1286,10 +1287,18 @@ extern "C" e2e_status e2e_autotune(e2e_ctx *ctx, const e2e_render_req *reqs, int
             if (st != E2E_OK) return st;
             keys[i] = tune_key(f, p, reqs[i].precision, reqs[i].spectrum_dtype);
             if (i == 0) table = p->kind == E2E_PSF_TABLE;
+            if (!table) continue;
+            const int tw = table_tw(p->kw);
+            const int c = table_chunk(((f->nx + tw - 1) / tw) * ((f->ny + kTableTH - 1) / kTableTH));
+            usual = i == 0 || c == usual ? c : 0;
         }
     }
     const bool batch = n > 1;
-    std::vector<int> chunks = table ? std::vector<int>{2, 4, 8, 16} : std::vector<int>{kTableChunk};
+    // the frames' own defaults first (0: of each by its size), kept on ties
+    std::vector<int> chunks{table ? usual : kTableChunk};
+    if (table)
+        for (int c : {2, 4, 8, 16})
+            if (c != usual) chunks.push_back(c);
     // a single-frame tuning keeps the batch width already chosen for the shape
     int keep_resident = 0;
     {
@@ -1297,8 +1306,9 @@ extern "C" e2e_status e2e_autotune(e2e_ctx *ctx, const e2e_render_req *reqs, int
         auto it = ctx->tune.find(keys[0]);
         if (it != ctx->tune.end()) keep_resident = it->second.resident;
     }
+    // (the other kinds' launches have one width)
     std::vector<int> residents =
-        batch ? std::vector<int>{1, 2, 3} : std::vector<int>{keep_resident};
+        batch && table ? std::vector<int>{3, 2, 1} : std::vector<int>{keep_resident};
     hipSetDevice(ctx->dev);
     hipStream_t s = reqs[0].hip_stream ? (hipStream_t)reqs[0].hip_stream : ctx->stream;
     hipEvent_t e0, e1;
