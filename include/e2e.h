@@ -443,6 +443,10 @@ e2e_status e2e_philox_blocks(e2e_ctx *ctx, uint64_t seed, uint32_t frame_index,
  * returns launches and total milliseconds per kernel name ("render_table",
  * "render_sep", "render_sep_mfma", "render_sfi", "plan", "noise",
  * "detector", "extract", "template_smooth", "ccf"), synchronising first.
+ * The render names go by what was asked for; launches of the column-node,
+ * split-tile and fiber-image-product kernels, which take such frames by a rule,
+ * are counted under "render_sep_fit", "render_sep_units" and
+ * "render_sfi_terms" as well.
  */
 e2e_status e2e_set_profiling(e2e_ctx *ctx, int32_t on);
 e2e_status e2e_kernel_time(e2e_ctx *ctx, const char *kernel, int64_t *launches,

@@ -203,7 +203,7 @@ static int tile_crowd(const std::vector<TraceDev> &tr, int nx, int ny)
     std::vector<Span> sp(ntx);
     for (const TraceDev &T : tr) {
         const double reach = 1.0 + 1e-6 + 2.0 * T.lmax * (1.5e5 / 299792458.0) / (T.lmax - T.lmin);
-        if (!(reach < 2.0)) {
+        if (!(reach < 64.0)) {  // (a span of a hundredth of its largest shift)
             ++everywhere;
             continue;
         }
@@ -1120,7 +1120,11 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
             int *counter = sc->counter + g;
             KernelCfg kc = cfg;
             kc.nodes = groups[g].nodes;
-            prof_begin(ctx, s, name);
+            const bool units = !mfma && kc.parts.part && kind != E2E_PSF_SFI;
+            prof_begin(ctx, s, name,
+                       kc.nodes == 0 ? (units ? "render_sep_units" : "")
+                       : kind == E2E_PSF_SFI ? "render_sfi_terms"
+                                             : "render_sep_fit");
             if (kind == E2E_PSF_TABLE)
                 q = launch_table(sc->frames_dev, kc, work, nwork, counter, sc->err, s);
             else if (kind == E2E_PSF_SFI && kc.nodes > 0)
@@ -1490,11 +1494,12 @@ extern "C" e2e_status e2e_philox_blocks(e2e_ctx *ctx, uint64_t seed, uint32_t fi
 
 // -------------------------------------------------------------- profiling
 
-void e2e::prof_begin(e2e_ctx *ctx, hipStream_t s, const char *name)
+void e2e::prof_begin(e2e_ctx *ctx, hipStream_t s, const char *name, const char *kernel)
 {
     if (!ctx->prof) return;
     ProfRec r;
     r.name = name;
+    r.kernel = kernel;
     hipEventCreate(&r.a);
     hipEventCreate(&r.b);
     hipEventRecord(r.a, s);
@@ -1521,9 +1526,12 @@ static void prof_collect(e2e_ctx *ctx)
         hipEventSynchronize(r.b);
         float ms = 0;
         if (hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
-            auto &acc = ctx->prof_acc[r.name];
-            acc.first += 1;
-            acc.second += ms;
+            for (const std::string *name : {&r.name, &r.kernel}) {
+                if (name->empty()) continue;
+                auto &acc = ctx->prof_acc[*name];
+                acc.first += 1;
+                acc.second += ms;
+            }
         }
         hipEventDestroy(r.a);
         hipEventDestroy(r.b);

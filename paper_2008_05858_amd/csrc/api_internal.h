@@ -88,7 +88,7 @@ struct NoAlloc {
 };
 
 struct ProfRec {
-    std::string name;
+    std::string name, kernel;   // kernel: also counted under this name (may be empty)
     hipEvent_t a = nullptr, b = nullptr;
 };
 
@@ -153,7 +153,7 @@ e2e_status run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool batc
 e2e_status check_err_word(int w);
 e2e_status take_err_word(Scratch *sc, hipStream_t s);
 std::string tune_key(const FormatRes *f, const PsfRes *p, int precision, int spectrum_dtype);
-void prof_begin(e2e_ctx *ctx, hipStream_t s, const char *name);
+void prof_begin(e2e_ctx *ctx, hipStream_t s, const char *name, const char *kernel = "");
 void prof_end(e2e_ctx *ctx, hipStream_t s);
 void serve_shutdown(e2e_ctx *ctx);
 
