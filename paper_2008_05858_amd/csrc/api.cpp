@@ -696,8 +696,10 @@ e2e_status e2e::validate_req(e2e_ctx *ctx, const e2e_render_req *r, FormatRes **
     return E2E_OK;
 }
 
-// Nodes a pixel column of the separable path's FP32 frames (k_sep_fit.hip),
-// 0 for the per-sample kernels.  kappa bounds the inverse width of a
+// Nodes a pixel column of the separable path's FP32 frames (k_sep_fit.hip: 10, 12,
+// or 13 for 12 nodes of a Gaussian narrow enough for its window, H / sigma^2 above
+// 13, to need the instance that looks for negative tails), 0 for the per-sample
+// kernels.  kappa bounds the inverse width of a
 // footprint along a trace (both axes, and the drift of sigma across a
 // column); the interpolation error 2.2 (kappa / 4)^M / sqrt(M!) of the peak
 // is kept below 4e-9, a tenth of the FP32 rounding of the frame: 10 nodes up
@@ -746,14 +748,18 @@ static int sep_fit_nodes(const FormatRes *F, const PsfRes *P, int precision, int
     const double kappa = std::hypot(1.0 / P->smin[0], F->slope / P->smin[1]) + drift;
     // the pixel integrals' own series, on either axis
     if (std::min(P->smin[0], P->smin[1]) < 0.58) return 0;
-    for (int M = 10; M <= 12; M += 2)
-        if (2.2 * std::pow(kappa / 4.0, M) <= 4e-9 * std::sqrt(std::tgamma(M + 1.0))) return M;
-    return 0;
+    auto enough = [&](int M) {
+        return 2.2 * std::pow(kappa / 4.0, M) <= 4e-9 * std::sqrt(std::tgamma(M + 1.0));
+    };
+    const double smin = std::min(P->smin[0], P->smin[1]);
+    return enough(10) ? 10 : !enough(12) ? 0 : P->H > 13.0 * smin * smin ? 13 : 12;
 }
 
 // Explicit fiber images of FP32 frames by k_sfi_terms.hip (1) or one by one
 // (0).  Its sub-pixel series fall as (1 / 2 sigma)^2k: eight terms leave 1e-9
-// of the peak at sigma = 0.58 px.  FP64 frames keep k_sfi.hip's own rounding.
+// of the peak at sigma = 0.58 px.  FP64 frames keep k_sfi.hip's own rounding.  No
+// line by the sub-pixel count: 983,040 images on 4096^2 take 1.85 ms here at S = 1,
+// 2 and 10, one by one 6.65, 6.98 and 9.85.
 static int sfi_terms(const FormatRes *F, const PsfRes *P, int out_dtype)
 {
     return P->kind == E2E_PSF_SFI && out_dtype == E2E_F32 && F->ntr <= kListTraces &&
@@ -1017,7 +1023,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
     // work list: frames by decreasing size, tiles in order
     sc->h_work.clear();
     // the frames of one launch share a kernel: work items [w0, w1) of each
-    // node count present (0, 10 and 12 for separable frames, 0 and 1 for SFI ones)
+    // node count present (0, 10, 12 and 13 for separable frames, 0 and 1 for SFI ones)
     struct Group {
         int nodes;
         size_t w0, w1;
@@ -1033,7 +1039,7 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         // frames of equal size go unit by unit, so the same unit of each (the
         // same spectrum ranges, read again under another Doppler shift) runs
         // at about the same time and its reads hit the caches
-        for (int nn : {0, 1, 10, 12}) {
+        for (int nn : {0, 1, 10, 12, 13}) {
             std::vector<int> own;
             for (int i : order)
                 if (nodes[i] == nn) own.push_back(i);

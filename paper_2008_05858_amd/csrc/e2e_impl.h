@@ -21,7 +21,7 @@ constexpr int kMfmaTH = 32;      // MFMA separable tile height (y)
 constexpr int kMaxTileTraces = 512;
 constexpr int kListTraces = 65535;   // traces of a frame that a tile's 16-bit list can name
 constexpr int kSepFitTiles = 768;   // tiles of a frame that fill the node path's workgroups
-constexpr int kCounters = 3;     // work-queue counters: one per render kernel of a batch
+constexpr int kCounters = 4;     // work-queue counters: one per render kernel of a batch
 constexpr int kSfiMaxR = 16;     // SFI: quadrature node pairs (32 nodes)
 constexpr int kSfiMaxH = 7;      // SFI: footprint half width
 constexpr int kSfiTW = 64;       // SFI tile width (x)
@@ -154,7 +154,7 @@ struct KernelCfg {
     int spec_f64;       // spectra element type
     int plain_tiles;    // plain launch: tiles of frame 0 (one block each)
     int precision;      // E2E_PREC_*
-    int nodes;          // separable: nodes a pixel column; SFI: 1 = product of terms;
+    int nodes;          // separable: nodes a pixel column (sep_fit_nodes); SFI: 1 = product of terms;
                         // 0 = the per-sample kernels
     SepParts parts;     // per-sample FP64 kernels of small frames
     int resident;       // persistent launches: workgroups per CU (0 = path default)

@@ -213,7 +213,7 @@ struct Vec4<double> {
     }
 };
 
-template <int DX, int DY, typename ST, int M, int SPAN>
+template <int DX, int DY, typename ST, int M, int SPAN, bool NARROW>
 __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__restrict__ frames,
                                                            const int2 *__restrict__ work,
                                                            int n_work, int *__restrict__ counter,
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
         const SegDev *segs = F.segs + (size_t)tx * ntr;
         int count = tile_traces(segs, ntr, ty, tid, smask, tlist, err);
         zero_lines(buf, tid);
-        if (M == 12 && tid == 0) sh_neg = 0;
+        if (NARROW && tid == 0) sh_neg = 0;
         __syncthreads();
         int zlo = 1, zhi = 0;  // lines this thread's node slot holds (none)
         double acc[2][4];
@@ -609,11 +609,12 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
             }
         }
         // Far from a narrow Gaussian's centre the interpolant can pass below zero, by
-        // 1e-20 of the photons (sigma 0.6 px, isolated bright samples; not with 10
-        // nodes, where sigma is 0.9 px at the least and w varies by e^10 over a column:
-        // the products' rounding shows from e^15).  So where a pixel is negative (rare)
-        // and none of the tile's samples is, it is zero.
-        if constexpr (M == 12) {
+        // 1e-20 of the photons (sigma 0.6 px, isolated bright samples): w varies by
+        // e^(z / sigma) over a column there, and the products' rounding shows from
+        // e^15 on.  So where a pixel is negative (rare) and none of the tile's samples
+        // is, it is zero.  (An instance of its own, for the frames whose windows reach
+        // that far: in every 12-node frame it took 1.6%.)
+        if constexpr (NARROW) {
             bool neg = false;
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb)
@@ -645,15 +646,15 @@ __global__ __launch_bounds__(256, 3) void k_render_sep_fit(const FrameDev *__res
     }
 }
 
-template <int DX, int DY, typename ST, int M>
+template <int DX, int DY, typename ST, int M, bool NARROW>
 hipError_t launch_m(const FrameDev *frames_dev, int precision, const int2 *work, int n_work,
                     int *counter, int *err, int nb, hipStream_t s)
 {
     if (precision == E2E_PREC_F64)
-        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, M, 4>), dim3(nb), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, M, 4, NARROW>), dim3(nb), dim3(256), 0, s,
                            frames_dev, work, n_work, counter, err);
     else
-        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, M, 16>), dim3(nb), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_render_sep_fit<DX, DY, ST, M, 16, NARROW>), dim3(nb), dim3(256), 0, s,
                            frames_dev, work, n_work, counter, err);
     return hipGetLastError();
 }
@@ -662,9 +663,12 @@ template <int DX, int DY, typename ST>
 hipError_t launch_st(const FrameDev *frames_dev, const KernelCfg &cfg, const int2 *work, int n_work,
                      int *counter, int *err, int nb, hipStream_t s)
 {
+    const int prec = cfg.precision;
     if (cfg.nodes == 10)
-        return launch_m<DX, DY, ST, 10>(frames_dev, cfg.precision, work, n_work, counter, err, nb, s);
-    return launch_m<DX, DY, ST, 12>(frames_dev, cfg.precision, work, n_work, counter, err, nb, s);
+        return launch_m<DX, DY, ST, 10, false>(frames_dev, prec, work, n_work, counter, err, nb, s);
+    if (cfg.nodes == 12)
+        return launch_m<DX, DY, ST, 12, false>(frames_dev, prec, work, n_work, counter, err, nb, s);
+    return launch_m<DX, DY, ST, 12, true>(frames_dev, prec, work, n_work, counter, err, nb, s);
 }
 
 template <int DX, int DY>

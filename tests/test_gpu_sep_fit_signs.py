@@ -40,3 +40,18 @@ def test_negative_samples_keep_their_sign(dtype):
     rq = Request(rv_mps=10.0)
     f, g = gpu_util.render(_scene(0.6, 8, 1.0, dtype), rq), gpu_util.render(_scene(0.6, 8, -1.0, dtype), rq)
     assert g.min() == -f.max() and np.max(np.abs(f + g)) < 1e-18 * f.max()
+
+
+def test_batch_of_every_kind_of_frame():
+    """Per sample, 10 nodes, 12, and 12 of a narrow Gaussian: each kernel has its own queue."""
+    from tests import gpu_util
+    scs = [_scene(s, h) for s, h in ((0.5, 6), (1.2, 8), (0.85, 6), (0.6, 8), (0.6, 8), (1.2, 8))]
+    lds = [gpu_util.P.Loaded(gpu_util.ctx(), sc) for sc in scs]
+    for prec in ("f64", "bf16_hilo"):
+        rqs = [Request(rv_mps=10.0 * i, flux_scale=1.0 + i, precision=prec) for i in range(len(scs))]
+        print(f"case signs batch {prec}", flush=True)
+        outs = gpu_util.render_batch(scs, rqs, lds)
+        for sc, ld, rq, o in zip(scs, lds, rqs, outs):
+            assert o.min() >= 0 and np.array_equal(o, gpu_util.render(sc, rq, loaded=ld))
+    for ld in lds:
+        ld.free()
