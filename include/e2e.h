@@ -72,15 +72,16 @@ typedef uint64_t e2e_ticket;
 #define E2E_FIBER_HALF_UP 1   /* its half at y >= the sample's y               */
 #define E2E_FIBER_HALF_DOWN 2 /* its half at y <= the sample's y               */
 
-/* arithmetic of the render path */
+/* arithmetic of the render path.  Under every precision, separable FP32 frames
+ * whose traces hold enough samples per pixel (6 to 34, more in small frames) are
+ * rendered from column nodes: FP64 weights rounded once to FP32, FP32 products
+ * added to FP64 sums, every 4 nodes under E2E_PREC_F64 and every 16 under the
+ * others.  The arithmetic named below is that of the other frames. */
 #define E2E_PREC_F64 0       /* FP64 positions, FP32 PSF offsets, FP64 sums    */
 #define E2E_PREC_F32 1       /* separable only: FP32 weights (fitted normal
                                 tail, Numerical Recipes Sec. 6.2) and FP32 sums */
 #define E2E_PREC_BF16_HILO 2 /* separable only: bf16 hi/lo MFMA, FP32 sums     */
 #define E2E_PREC_F16_HILO 3  /* separable only: fp16 hi/lo MFMA, FP32 sums     */
-/* (separable FP32 frames whose traces hold enough samples per pixel are
- * rendered from column nodes: FP64 weights rounded once to FP32, FP32 products
- * of 16 nodes added to FP64 sums, at every precision) */
 
 /* request flags */
 #define E2E_FLAG_ASYNC 1u    /* device output: return once enqueued on stream  */
@@ -94,7 +95,7 @@ typedef uint64_t e2e_ticket;
 typedef struct {
     int32_t order, fiber, slice;
     double lambda_min_nm, lambda_max_nm;
-    int64_t n_samples;            /* 1 .. 2^31-1                              */
+    int64_t n_samples;            /* 1 .. 2^31-2                              */
     int32_t deg_x, deg_y;
     const double *cx, *cy;
     double throughput;
