@@ -328,7 +328,7 @@ extern "C" e2e_status e2e_format_load(e2e_ctx *ctx, const e2e_trace_desc *tr, in
         dym = std::max(dym, T.degy);
         nslots = std::max(nslots, T.slot + 1);
     }
-    const int crowd = n <= kMaxTileTraces ? n : tile_crowd(h, nx, ny);
+    const int crowd = n <= kMaxTileTraces || n > kListTraces ? n : tile_crowd(h, nx, ny);
     hipSetDevice(ctx->dev);
     size_t bytes = sizeof(TraceDev) * n;
     std::lock_guard<std::mutex> lk(ctx->mu);
