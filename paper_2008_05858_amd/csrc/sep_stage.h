@@ -1,8 +1,8 @@
 // Shared by the render kernels that multiply separable terms on the matrix
 // cores (k_sep_fit.hip, k_sfi_terms.hip): a 64 x 32 pixel tile, chunks of 120
 // nodes whose column rows (x) and row rows (y) are staged in LDS in operand
-// layout, F += Gy^T Gx by v_mfma_f32_16x16x4_f32, FP32 partials of 16 nodes
-// added to FP64 sums.
+// layout, F += Gy^T Gx by v_mfma_f32_16x16x4_f32, FP32 partials of 4, 8 or 16
+// nodes added to FP64 sums (each kernel says which it takes, and why).
 #pragma once
 
 #include "psf_gauss.h"
