@@ -921,8 +921,9 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         (kind == E2E_PSF_SEPARABLE && prec == E2E_PREC_F64))
         for (int i = 0; i < n; ++i) sep_items += nodes[i] == 0 ? tiles[i] : 0;
     const size_t part_bytes = sep_items * kSepUnits * 256 * sizeof(double);
-    if (!noalloc && sep_items > 0 && sep_items <= kSepSplitItems) {
-        const size_t need = part_bytes + sep_items * sizeof(int);
+    const size_t need = part_bytes + sep_items * sizeof(int);
+    const bool split = !noalloc && sep_items > 0 && sep_items <= kSepSplitItems;
+    if (split) {
         const size_t more = need > sc->parts_cap ? need - sc->parts_cap : 0;
         if (more > 0 && ctx->loop_ws && !fits_beside(ctx, temp_bytes + scratch_need + more)) {
             ctx->kept -= ctx->loop_cap;   // (idle: its call's stream has passed)
@@ -942,8 +943,6 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
                 (void)hipGetLastError();  // no memory for them: without
             }
         }
-        if (sc->parts_cap >= need)
-            cfg.parts = {reinterpret_cast<int *>((char *)sc->parts + part_bytes), (double *)sc->parts};
     }
 
     // spectra pointers (device), host spectra copied to temporaries
@@ -1019,6 +1018,9 @@ e2e_status e2e::run_frames(e2e_ctx *ctx, const e2e_render_req *reqs, int n, bool
         F.frame_index = r.frame_index;
         F.seed = r.seed;
     }
+    // after the call's last allocation: one that the device refuses gives the sums back
+    if (split && sc->parts_cap >= need)
+        cfg.parts = {reinterpret_cast<int *>((char *)sc->parts + part_bytes), (double *)sc->parts};
     cfg.plain_tiles = tiles[0];
     // work list: frames by decreasing size, tiles in order
     sc->h_work.clear();
